@@ -604,7 +604,7 @@ size_t tactic_build_clusters_workspace_size(const tactic_kv_shape* shape, int64_
                                             int32_t max_clusters) {
   if (check_shape(shape) != TACTIC_OK || max_clusters < 1 || total_clusters < max_clusters) return 0;
   return tactic::kmeans_workspace_bytes(shape->batch, shape->n_kv_heads, shape->total_tokens,
-                                        total_clusters, max_clusters, shape->max_seq_len);
+                                        total_clusters);
 }
 
 tactic_status tactic_build_clusters(const uint16_t* K, const uint16_t* V, const tactic_kv_shape* shape,

@@ -7,7 +7,7 @@
 
 namespace tactic {
 
-size_t kmeans_workspace_bytes(int B, int Hkv, int64_t total, int64_t Ct, int Cm, int64_t nmax);
+size_t kmeans_workspace_bytes(int B, int Hkv, int64_t total, int64_t Ct);
 
 hipError_t run_kmeans(const uint16_t* K, const uint16_t* V, const int64_t* kv_indptr, const int64_t* seq_len,
                       const int64_t* cl_indptr, int B, int Hkv, int64_t total, int64_t nmax,
