@@ -40,10 +40,13 @@ namespace tactic {
 
 constexpr int kAsgTok = 256;        // tokens per assignment workgroup (4 waves x 64)
 constexpr int kAsgCen = 96;         // centroids staged in LDS per step
-constexpr int kListCen = 4 * kAsgCen;  // centroids per work item of the listed keys
-constexpr int kSliceMax = 8192;     // clusters per slice of the update and layout kernels (8 per thread)
+constexpr int kListCen = 2 * kAsgCen;  // centroids per work item of the listed keys
+constexpr int kSliceMax = 4096;     // clusters per slice of the update and layout kernels
+constexpr int kSliceCap = 4096;     // keys per slice that they collect in LDS
 constexpr int kRankMax = 256;       // members ranked by counting in LDS; beyond, by a bitmap of tokens
-constexpr int kBitTokens = 16384;   // tokens per bitmap window (2 KB of LDS per wave)
+constexpr int kOrdWords = 512;      // words of LDS per wave for sorting members
+constexpr int kBitTokens = kOrdWords * 32;  // tokens per bitmap window
+constexpr int kSmall = 64;          // members of a cluster that one wave takes in one go
 constexpr int kStateInts = 64;      // counters of a problem, each in a 64-byte line of its own
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -466,7 +469,7 @@ __global__ __launch_bounds__(1024) void km_merge_kernel(KmArgs a) {
 }
 
 // One pass of a workgroup (1024 threads) over a problem's assignments: f(token,
-// cluster) for every token, kIn loads in flight per thread.
+// cluster) for every token, 16 loads in flight per thread.
 template <typename F>
 __device__ __forceinline__ void for_tokens(const int32_t* assign, int n, F f) {
   constexpr int kIn = 16;
@@ -478,6 +481,51 @@ __device__ __forceinline__ void for_tokens(const int32_t* assign, int n, F f) {
     for (int k = 0; k < kIn; ++k)
       if (i0 + 1024 * k < n) f((int)(i0 + 1024 * k), c[k]);
   }
+}
+
+// Collects the tokens of the clusters [c_beg, c_beg + nc) in LDS, in no fixed
+// order, and returns how many there are (only the first kSliceCap are kept);
+// `before`, if given, is this thread's count of keys of earlier clusters.  One
+// pass over the assignments, 16 loads in flight per thread: a wave
+// reserves places for all its hits of a step at once, and each thread
+// walks the bits of its own hits (an LDS counter update per key, waited for,
+// had taken 15 us per pass over 65536 keys, bound by instruction issue).
+// Ends with a barrier; *s_total is 0 before.
+__device__ __forceinline__ int collect_slice(const int32_t* assign, int n, int c_beg, int nc, int32_t* s_tok, int* s_total,
+                                             int* before = nullptr) {
+  constexpr int kIn = 16;
+  const int tid = threadIdx.x, lane = tid & 63;
+  int nb = 0;
+  int c[kIn];
+  auto load = [&](int64_t i0) {
+#pragma unroll
+    for (int k = 0; k < kIn; ++k) {
+      const int64_t i = i0 + tid + 1024 * k;
+      const int x = assign[min(i, (int64_t)n - 1)];
+      c[k] = i < n ? x : 0x7fffffff;
+    }
+  };
+  if (n > 0) load(0);
+  for (int64_t i0 = 0; i0 < n; i0 += 1024 * kIn) {
+    uint32_t bits = 0;
+#pragma unroll
+    for (int k = 0; k < kIn; ++k) {
+      if (before) nb += c[k] < c_beg ? 1 : 0;
+      bits |= (uint32_t)(c[k] - c_beg) < (uint32_t)nc ? 1u << k : 0u;
+    }
+    if (i0 + 1024 * kIn < n) load(i0 + 1024 * kIn);  // travels during the stores below
+    const int mine = __popc(bits), incl = wave_incl_scan(mine);
+    const int hits = __builtin_amdgcn_readlane(incl, 63);
+    if (hits == 0) continue;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(s_total, hits);
+    int pos = __builtin_amdgcn_readfirstlane(at) + incl - mine;
+    for (; bits; bits &= bits - 1, ++pos)
+      if (pos < kSliceCap) s_tok[pos] = (int)i0 + tid + 1024 * (__ffs((int)bits) - 1);
+  }
+  if (before) *before = nb;
+  __syncthreads();
+  return *s_total;
 }
 
 // Exclusive scan in place of s[0..count) (count <= kSliceMax) in LDS by 1024
@@ -508,19 +556,39 @@ __device__ __forceinline__ int slice_scan(int32_t* s, int count, int mine, int* 
   return sum;
 }
 
-// One wave sorts a cluster's m members (tokens below n) by token: into s_w (up to
-// kRankMax members, counted ranks), else into `out` (a bitmap of the tokens,
-// window by window); rank[token] = its place.  s_w: the wave's 2 KB of LDS.
+// Values of y below x among lanes [0, km) of the wave (lanes from km on hold the
+// largest value): lane reads at constant lanes, 16 at a time (a read at a
+// lane number in a register took about 100 cycles).
+__device__ __forceinline__ int count_below(int y, int x, int km) {
+  int r = 0;
+#pragma unroll
+  for (int k0 = 0; k0 < 64; k0 += 16) {
+    if (k0 < km) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) r += __builtin_amdgcn_readlane(y, k0 + k) < x ? 1 : 0;
+    }
+  }
+  return r;
+}
+
+// One wave sorts a cluster's m <= 64 members by token into s_w; rank[token] = its place.
+__device__ __forceinline__ void sort_small(const int32_t* list, int m, uint32_t* s_w, int32_t* rank, int lane) {
+  const int x = lane < m ? list[lane] : 0x7fffffff;
+  const int r = count_below(x, x, m);
+  if (lane < m) {
+    s_w[r] = (uint32_t)x;
+    rank[x] = r;
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The same for any m (tokens below n): into s_w (kOrdWords words) up to
+// kRankMax members (counted ranks), else into `out` (a bitmap of the tokens,
+// window by window).
 __device__ __forceinline__ void sort_members(const int32_t* list, int m, int n, uint32_t* s_w, int32_t* out, int32_t* rank,
                                              int lane) {
   if (m <= 64) {
-    const int x = lane < m ? list[lane] : 0x7fffffff;
-    int r = 0;
-    for (int i = 0; i < m; ++i) r += __builtin_amdgcn_readlane(x, i) < x ? 1 : 0;
-    if (lane < m) {
-      s_w[r] = (uint32_t)x;
-      rank[x] = r;
-    }
+    sort_small(list, m, s_w, rank, lane);
   } else if (m <= kRankMax) {
     constexpr int kE = kRankMax / 64;
     int x[kE], r[kE];
@@ -576,23 +644,34 @@ __device__ __forceinline__ void sort_members(const int32_t* list, int m, int n, 
 
 // ---------------------------------------------------------------------------
 // centroid = bf16(mean of members), of the slice's clusters that gained or lost a
-// key (all of them in the first iteration): their member lists, collected by
-// two passes over the problem's assignments (counts and cursors in LDS:
-// device-wide atomics, one per token, took 36 us at 65536 x 8 against about
-// 6), sorted by token, then the means, a wave per cluster.
+// key (all of them in the first iteration).  Their members, collected in LDS
+// by one pass over the assignments, are sorted by token and summed:
+//  - a wave per cluster of up to 64 members, the next cluster's members sorted
+//    while this one's rows are in flight;
+//  - larger ones (on a mixture, a centroid between components collects the keys
+//    of many: 500 to 1000 of 65536) by four waves, one for each of the four
+//    interleaved chains that every sum consists of, with 32 rows of a chain
+//    in flight (16 rows at a time in one wave, the largest cluster had set the
+//    kernel's time).
+// 65536 x 8 keys: 116 us in the first iteration (the gather of every key), 21 to
+// 36 later, against 134 and 35 to 55 with a wave for every cluster.
+// A slice of more than kSliceCap keys (few clusters) takes two passes and lists
+// in memory, a wave per cluster.
 // grid (slices, BG), 1024 threads; per: clusters per slice
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
-  extern __shared__ __align__(16) int32_t s_dyn[];  // [per] starts, [per] ends, [per] dirty / place among the changed
-  __shared__ __align__(16) uint32_t s_list[16][kBitTokens / 32];
-  __shared__ int s_w[32], s_n, s_base;
+  extern __shared__ __align__(16) int32_t s_dyn[];  // [per] starts, [per] sizes, [per] dirty / place among the changed
+  __shared__ __align__(16) uint32_t s_ord[16][kOrdWords];
+  __shared__ int32_t s_tok[kSliceCap], s_mem[kSliceCap];
+  __shared__ int s_big[kSliceCap / kSmall];
+  __shared__ int s_w[32], s_n, s_base, s_total, s_nbig;
   const int p = blockIdx.y;
   if (*done_flag(a, p)) return;
   const Problem q = problem(a, p);
   const int c_beg = blockIdx.x * per, nc = min(per, q.C - c_beg);
   if (nc <= 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sl = lane & 15, grp = lane >> 4;
-  int32_t *s_beg = s_dyn, *s_end = s_dyn + per, *s_slot = s_dyn + 2 * per;
+  int32_t *s_beg = s_dyn, *s_cnt = s_dyn + per, *s_slot = s_dyn + 2 * per;
   int any = 0;
   for (int c = tid; c < nc; c += 1024) {
     const int64_t at = q.cl_base + c_beg + c;
@@ -603,91 +682,216 @@ __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
     a.dirty[at] = 0;
     a.moved[at] = 0;
   }
-  if (tid == 0) s_n = 0;
+  if (tid == 0) s_n = s_total = s_nbig = 0;
   if (!__syncthreads_or(any)) return;
   const int32_t* assign = a.assign + q.tok_base;
-  int before = 0;  // keys of the clusters before the slice
-  for_tokens(assign, q.n, [&](int, int c) {
-    before += c < c_beg ? 1 : 0;
-    const uint32_t k = (uint32_t)(c - c_beg);
-    if (k < (uint32_t)nc && s_slot[k]) atomicAdd(&s_beg[k], 1);
-  });
+  int32_t* rank = a.rank + q.tok_base;
+  int before = 0;  // keys of the clusters before the slice (used by the lists in memory)
+  const int total = collect_slice(assign, q.n, c_beg, nc, s_tok, &s_total);
+  const bool in_lds = total <= kSliceCap;
+  constexpr int kE = kSliceCap / 1024;
+  int tok_e[kE], cl_e[kE], place[kE];
+  if (in_lds) {
+#pragma unroll
+    for (int e = 0; e < kE; ++e) {
+      tok_e[e] = s_tok[max(min(tid + 1024 * e, total - 1), 0)];  // (unused when total is 0)
+      place[e] = -1;
+    }
+#pragma unroll
+    for (int e = 0; e < kE; ++e) cl_e[e] = tid + 1024 * e < total ? assign[tok_e[e]] - c_beg : -1;
+#pragma unroll
+    for (int e = 0; e < kE; ++e)
+      if (cl_e[e] >= 0 && s_slot[cl_e[e]]) place[e] = atomicAdd(&s_beg[cl_e[e]], 1);
+  } else {
+    for_tokens(assign, q.n, [&](int, int c) {
+      before += c < c_beg ? 1 : 0;
+      const uint32_t k = (uint32_t)(c - c_beg);
+      if (k < (uint32_t)nc && s_slot[k]) atomicAdd(&s_beg[k], 1);
+    });
+  }
+  __syncthreads();
+  for (int c = tid; c < nc; c += 1024) {
+    const int m = s_beg[c];
+    s_cnt[c] = m;
+    if (m == 0) s_slot[c] = -1;  // nothing to do: an empty cluster keeps its centroid
+    else if (in_lds && m > kSmall) s_big[atomicAdd(&s_nbig, 1)] = c;
+  }
   __syncthreads();
   before = slice_scan(s_beg, nc, before, s_w);
-  for (int c = tid; c < nc; c += 1024) s_end[c] = s_beg[c];
-  __syncthreads();
   int32_t* members = a.members + q.tok_base + before;
-  const int room = q.n - before;  // (the lists of the slice's clusters fit: they are disjoint)
-  for_tokens(assign, q.n, [&](int t, int c) {
-    const uint32_t k = (uint32_t)(c - c_beg);
-    if (k < (uint32_t)nc && s_slot[k]) members[min(atomicAdd(&s_end[k], 1), room - 1)] = t;
-  });
-  __threadfence_block();
+  if (in_lds) {
+#pragma unroll
+    for (int e = 0; e < kE; ++e)
+      if (place[e] >= 0) s_mem[s_beg[cl_e[e]] + place[e]] = tok_e[e];
+  } else {
+    const int room = q.n - before;  // (the lists of the slices' clusters fit: they are disjoint)
+    for_tokens(assign, q.n, [&](int t, int c) {
+      const uint32_t k = (uint32_t)(c - c_beg);
+      if (k < (uint32_t)nc && s_cnt[k] > 0) members[min(atomicAdd(&s_beg[k], 1), room - 1)] = t;
+    });
+    __syncthreads();
+    for (int c = tid; c < nc; c += 1024) s_beg[c] -= s_cnt[c];  // the cursors ended at the lists' ends
+    __threadfence_block();
+  }
   __syncthreads();
-  for (int c = wave; c < nc; c += 16) {
+
+  // cluster c of m members with the sums s of its lane's 8 dimensions (the same
+  // in the four lane-groups): store the centroid if it changed
+  auto finish = [&](int c, int m, const float (&s)[8], const uint4& old) {
     const int64_t at = q.cl_base + c_beg + c;
-    const int b0 = s_beg[c], m = s_end[c] - b0;
-    int slot = -1;
-    if (m > 0) {  // an empty cluster keeps its centroid
-      const uint4 old = *reinterpret_cast<const uint4*>(a.centroids + at * kHeadDim + sl * 8);
-      uint32_t* s_ord = s_list[wave];
-      int32_t* sorted = a.perm + q.tok_base + before + b0;  // (scratch until km_layout)
-      sort_members(members + b0, m, q.n, s_ord, sorted, a.rank + q.tok_base, lane);
-      // lane-group grp sums members grp, grp + 4, grp + 8, ... in that
-      // order; 16 rows per step, their key rows loaded together
-      float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      for (int r0 = 0; r0 < m; r0 += 16) {
-        int tok[4];
-        if (m <= kRankMax) {
+    const float inv = 1.f / (float)m;
+    float cn = 0.f;
+    uint32_t out[4];
 #pragma unroll
-          for (int k = 0; k < 4; ++k) tok[k] = (int)s_ord[min(r0 + grp + 4 * k, m - 1)];
-        } else {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) tok[k] = sorted[min(r0 + grp + 4 * k, m - 1)];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) tok[k] = min(max(tok[k], 0), q.n - 1);
-        uint4 v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          v[k] = *reinterpret_cast<const uint4*>(a.K + (q.tok_base + tok[k]) * kHeadDim + sl * 8);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (r0 + grp + 4 * k >= m) continue;
-          const uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            s[2 * e] += bf16lo(w[e]);
-            s[2 * e + 1] += bf16hi(w[e]);
-          }
-        }
+    for (int e = 0; e < 8; ++e) {
+      const uint16_t hb = f32_to_bf16_rne(s[e] * inv);
+      const float r = __uint_as_float((uint32_t)hb << 16);
+      cn = fmaf(r, r, cn);
+      if (e & 1) out[e >> 1] |= (uint32_t)hb << 16;
+      else out[e >> 1] = hb;
+    }
+    cn = sum16(cn);
+    const bool moved = __any(out[0] != old.x || out[1] != old.y || out[2] != old.z || out[3] != old.w);
+    if (moved && grp == 0)
+      *reinterpret_cast<uint4*>(a.centroids + at * kHeadDim + sl * 8) = make_uint4(out[0], out[1], out[2], out[3]);
+    if (lane == 0) {
+      if (moved) {
+        a.cnorm[at] = cn;
+        a.moved[at] = 1;
       }
-      const float inv = 1.f / (float)m;
-      float cn = 0.f;
-      uint32_t out[4];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        float v = s[e];
-        v += __shfl_xor(v, 16, 64);
-        v += __shfl_xor(v, 32, 64);
-        const uint16_t hb = f32_to_bf16_rne(v * inv);
-        const float r = __uint_as_float((uint32_t)hb << 16);
-        cn = fmaf(r, r, cn);
-        if (e & 1) out[e >> 1] |= (uint32_t)hb << 16;
-        else out[e >> 1] = hb;
-      }
-      cn = sum16(cn);
-      if (__any(out[0] != old.x || out[1] != old.y || out[2] != old.z || out[3] != old.w)) {
-        if (grp == 0) *reinterpret_cast<uint4*>(a.centroids + at * kHeadDim + sl * 8) =
-            make_uint4(out[0], out[1], out[2], out[3]);
-        if (lane == 0) {
-          a.cnorm[at] = cn;
-          a.moved[at] = 1;
-          slot = atomicAdd(&s_n, 1);
+      s_slot[c] = moved ? atomicAdd(&s_n, 1) : -1;
+    }
+  };
+
+  // ---- clusters of more than kSmall members
+  const int nbig = __builtin_amdgcn_readfirstlane(s_nbig);
+  if (nbig > 0) {
+    // their members by token into s_tok: a wave ranks 64 members of a cluster
+    // against all of its members
+    int task = 0;
+    for (int i = 0; i < nbig; ++i) {
+      const int c = __builtin_amdgcn_readfirstlane(s_big[i]);
+      const int b0 = __builtin_amdgcn_readfirstlane(s_beg[c]), m = __builtin_amdgcn_readfirstlane(s_cnt[c]);
+      for (int j0 = 0; j0 < m; j0 += 64, ++task) {
+        if ((task & 15) != wave) continue;
+        const int x = j0 + lane < m ? s_mem[b0 + j0 + lane] : 0x7fffffff;
+        int r = 0;
+        for (int k0 = 0; k0 < m; k0 += 64) {
+          const int y = k0 + lane < m ? s_mem[b0 + k0 + lane] : 0x7fffffff;
+          r += count_below(y, x, m - k0);
+        }
+        if (j0 + lane < m) {
+          s_tok[b0 + r] = x;
+          rank[x] = r;
         }
       }
     }
-    if (lane == 0) s_slot[c] = slot;
+    __syncthreads();
+    float* s_part = reinterpret_cast<float*>(s_ord);  // [4 clusters][4 chains][128]
+    const int quad = wave >> 2, chain = wave & 3;
+    for (int i0 = 0; i0 < nbig; i0 += 4) {
+      const bool on = i0 + quad < nbig;
+      const int c = __builtin_amdgcn_readfirstlane(on ? s_big[i0 + quad] : 0);
+      const int b0 = __builtin_amdgcn_readfirstlane(s_beg[c]), m = on ? __builtin_amdgcn_readfirstlane(s_cnt[c]) : 0;
+      uint4 old = make_uint4(0, 0, 0, 0);
+      if (on && chain == 0) old = *reinterpret_cast<const uint4*>(a.centroids + (q.cl_base + c_beg + c) * kHeadDim + sl * 8);
+      // the chain's rows chain, chain + 4, ...; this lane's two dimensions
+      float s0 = 0.f, s1 = 0.f;
+      const uint32_t* Kl = reinterpret_cast<const uint32_t*>(a.K + q.tok_base * kHeadDim) + lane;
+      const int nr = (m - chain + 3) / 4;
+      for (int r0 = 0; r0 < nr; r0 += 64) {
+        const int t = s_tok[b0 + min(chain + 4 * (r0 + lane), m - 1)];
+        const int rm = min(64, nr - r0);
+#pragma unroll
+        for (int k0 = 0; k0 < 64; k0 += 32) {
+          if (k0 >= rm) break;
+          uint32_t v[32];  // (lanes past the end hold the last row again)
+#pragma unroll
+          for (int k = 0; k < 32; ++k)
+            v[k] = Kl[(int64_t)min(max(__builtin_amdgcn_readlane(t, k0 + k), 0), q.n - 1) * (kHeadDim / 2)];
+#pragma unroll
+          for (int k = 0; k < 32; ++k)
+            if (k0 + k < rm) {
+              s0 += bf16lo(v[k]);
+              s1 += bf16hi(v[k]);
+            }
+        }
+      }
+      if (on) *reinterpret_cast<float2*>(s_part + (quad * 4 + chain) * kHeadDim + 2 * lane) = make_float2(s0, s1);
+      __syncthreads();
+      if (on && chain == 0) {
+        float s[8];
+        const float* x = s_part + quad * 4 * kHeadDim + sl * 8;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          s[e] = (x[e] + x[kHeadDim + e]) + (x[2 * kHeadDim + e] + x[3 * kHeadDim + e]);
+        finish(c, m, s, old);
+      }
+      __syncthreads();  // s_part is rewritten
+    }
+  }
+
+  // ---- the others: a wave per cluster
+  auto next = [&](int c) {  // this wave's clusters, from c on
+    while (c < nc && (s_cnt[c] == 0 || (in_lds && s_cnt[c] > kSmall))) c += 16;
+    return __builtin_amdgcn_readfirstlane(c);
+  };
+  constexpr int kHalf = kOrdWords / 2;  // (two buffers of up to kSmall members, or one of the lists in memory)
+  auto sort = [&](int c, int buf) {
+    const int b0 = __builtin_amdgcn_readfirstlane(s_beg[c]), m = __builtin_amdgcn_readfirstlane(s_cnt[c]);
+    if (in_lds) sort_small(s_mem + b0, m, s_ord[wave] + buf * kHalf, rank, lane);
+    else sort_members(members + b0, m, q.n, s_ord[wave], a.perm + q.tok_base + before + b0, rank, lane);  // (perm: scratch)
+  };
+  int c = next(wave);
+  if (c < nc && in_lds) sort(c, 0);
+  for (int buf = 0; c < nc; buf ^= 1) {
+    const int b0 = __builtin_amdgcn_readfirstlane(s_beg[c]), m = __builtin_amdgcn_readfirstlane(s_cnt[c]);
+    const uint4 old = *reinterpret_cast<const uint4*>(a.centroids + (q.cl_base + c_beg + c) * kHeadDim + sl * 8);
+    if (!in_lds) sort(c, 0);
+    const uint32_t* ord = s_ord[wave] + (in_lds ? buf * kHalf : 0);
+    const int32_t* sorted = a.perm + q.tok_base + before + b0;
+    // lane-group grp sums members grp, grp + 4, grp + 8, ... in that order;
+    // 16 rows per step, their key rows loaded together
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    uint4 v[4];
+    auto load = [&](int r0) {
+      int tok[4];
+      if (in_lds || m <= kRankMax) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tok[k] = (int)ord[min(r0 + grp + 4 * k, m - 1)];
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tok[k] = sorted[min(r0 + grp + 4 * k, m - 1)];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) tok[k] = min(max(tok[k], 0), q.n - 1);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        v[k] = *reinterpret_cast<const uint4*>(a.K + (q.tok_base + tok[k]) * kHeadDim + sl * 8);
+    };
+    load(0);
+    const int c_next = next(c + 16);
+    if (c_next < nc && in_lds) sort(c_next, buf ^ 1);
+    for (int r0 = 0; r0 < m; r0 += 16) {
+      if (r0 > 0) load(r0);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (r0 + grp + 4 * k >= m) continue;
+        const uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s[2 * e] += bf16lo(w[e]);
+          s[2 * e + 1] += bf16hi(w[e]);
+        }
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      s[e] += __shfl_xor(s[e], 16, 64);
+      s[e] += __shfl_xor(s[e], 32, 64);
+    }
+    finish(c, m, s, old);
+    c = c_next;
   }
   // the changed centroids join the problem's list (its order does not matter:
   // equal scores among them list the key); the rows written above are read back
@@ -696,14 +900,14 @@ __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
   if (s_n == 0) return;
   if (tid == 0) s_base = atomicAdd(n_moved(a, p), s_n);
   __syncthreads();
-  for (int c = tid >> 4; c < nc; c += 64) {
-    if (s_slot[c] < 0) continue;
-    const int64_t at = q.cl_base + c_beg + c, to = q.cl_base + s_base + s_slot[c];
+  for (int j = tid >> 4; j < nc; j += 64) {
+    if (s_slot[j] < 0) continue;
+    const int64_t at = q.cl_base + c_beg + j, to = q.cl_base + s_base + s_slot[j];
     *reinterpret_cast<uint4*>(a.d_rows + to * kHeadDim + sl * 8) =
         *reinterpret_cast<const uint4*>(a.centroids + at * kHeadDim + sl * 8);
     if (sl == 0) {
       a.d_norm[to] = a.cnorm[at];
-      a.d_id[to] = c_beg + c;
+      a.d_id[to] = c_beg + j;
     }
   }
 }
@@ -714,28 +918,56 @@ __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void km_layout_kernel(KmArgs a, int per) {
   extern __shared__ __align__(16) int32_t s_dyn[];  // [per] rows before each cluster
-  __shared__ int s_w[32];
+  __shared__ int32_t s_tok[kSliceCap];
+  __shared__ int s_w[32], s_total;
   const int p = blockIdx.y;
   const Problem q = problem(a, p);
   if (blockIdx.x == 0 && threadIdx.x == 0) a.offsets[q.off_base + q.C] = q.n;
   const int c_beg = blockIdx.x * per, nc = min(per, q.C - c_beg);
   if (nc <= 0) return;
-  for (int c = threadIdx.x; c < nc; c += 1024) s_dyn[c] = 0;
+  const int tid = threadIdx.x;
+  for (int c = tid; c < nc; c += 1024) s_dyn[c] = 0;
+  if (tid == 0) s_total = 0;
   __syncthreads();
   const int32_t* assign = a.assign + q.tok_base;
+  const int32_t* rank = a.rank + q.tok_base;
+  int32_t* perm = a.perm + q.tok_base;
   int before = 0;
-  for_tokens(assign, q.n, [&](int, int c) {
-    before += c < c_beg ? 1 : 0;
-    const uint32_t k = (uint32_t)(c - c_beg);
-    if (k < (uint32_t)nc) atomicAdd(&s_dyn[k], 1);
-  });
+  const int total = collect_slice(assign, q.n, c_beg, nc, s_tok, &s_total, &before);
+  const bool in_lds = total <= kSliceCap;
+  constexpr int kE = kSliceCap / 1024;
+  int tok_e[kE], cl_e[kE], rk[kE];
+  if (in_lds) {
+#pragma unroll
+    for (int e = 0; e < kE; ++e) tok_e[e] = s_tok[max(min(tid + 1024 * e, total - 1), 0)];  // (unused when total is 0)
+#pragma unroll
+    for (int e = 0; e < kE; ++e) {
+      const bool in = tid + 1024 * e < total;
+      cl_e[e] = in ? assign[tok_e[e]] - c_beg : -1;
+      rk[e] = in ? rank[tok_e[e]] : 0;
+    }
+#pragma unroll
+    for (int e = 0; e < kE; ++e)
+      if (cl_e[e] >= 0) atomicAdd(&s_dyn[cl_e[e]], 1);
+  } else {
+    for_tokens(assign, q.n, [&](int, int c) {
+      const uint32_t k = (uint32_t)(c - c_beg);
+      if (k < (uint32_t)nc) atomicAdd(&s_dyn[k], 1);
+    });
+  }
   __syncthreads();
   before = slice_scan(s_dyn, nc, before, s_w);
-  for (int c = threadIdx.x; c < nc; c += 1024) a.offsets[q.off_base + c_beg + c] = before + s_dyn[c];
-  for_tokens(assign, q.n, [&](int t, int c) {
-    const uint32_t k = (uint32_t)(c - c_beg);
-    if (k < (uint32_t)nc) a.perm[q.tok_base + min(max(before + s_dyn[k] + a.rank[q.tok_base + t], 0), q.n - 1)] = t;
-  });
+  for (int c = tid; c < nc; c += 1024) a.offsets[q.off_base + c_beg + c] = before + s_dyn[c];
+  if (in_lds) {
+#pragma unroll
+    for (int e = 0; e < kE; ++e)
+      if (cl_e[e] >= 0) perm[min(max(before + s_dyn[cl_e[e]] + rk[e], 0), q.n - 1)] = tok_e[e];
+  } else {
+    for_tokens(assign, q.n, [&](int t, int c) {
+      const uint32_t k = (uint32_t)(c - c_beg);
+      if (k < (uint32_t)nc) perm[min(max(before + s_dyn[k] + rank[t], 0), q.n - 1)] = t;
+    });
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -841,9 +1073,11 @@ hipError_t run_kmeans(const uint16_t* K, const uint16_t* V, const int64_t* kv_in
   a.K_sorted = K_sorted;
   a.V_sorted = V_sorted;
   const dim3 g_cl((Cm + 3) / 4, BG), g_tok((unsigned)((nmax + kAsgTok - 1) / kAsgTok), BG);
-  // slices of the clusters: one workgroup each on the 256 compute units, at
-  // least 16 clusters (a wave each) and at most kSliceMax per slice
-  const int per = std::min(kSliceMax, std::max(16, (Cm + std::max(1, 256 / BG) - 1) / std::max(1, 256 / BG)));
+  // slices of the clusters: at least one workgroup for each of the 256 compute
+  // units and few enough keys per slice for LDS (half of kSliceCap on
+  // average), at least 16 clusters (a wave each) and at most kSliceMax
+  const int64_t ns = std::max<int64_t>((256 + BG - 1) / BG, (nmax + kSliceCap / 2 - 1) / (kSliceCap / 2));
+  const int per = (int)std::min<int64_t>(kSliceMax, std::max<int64_t>(16, (Cm + ns - 1) / ns));
   const dim3 g_slice((Cm + per - 1) / per, BG);
   const size_t lds_upd = (size_t)per * 12, lds_lay = (size_t)per * 4;
   // listed keys: work items in flight per problem, three workgroups on each of
