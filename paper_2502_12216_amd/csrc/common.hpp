@@ -33,16 +33,25 @@ __device__ __forceinline__ int64_t seq_tokens(const int64_t* indptr, const int64
   return len ? max((int64_t)0, min(l, span)) : span;
 }
 
+// floor((n * bp + add) / 10000) for 0 <= n < 2^31, 0 <= bp <= 10000, add < 10000,
+// in 32 bits: with n = 10000 a + r the quotient is a bp + floor((r bp + add) / 10000)
+__host__ __device__ inline int64_t bp_of(uint32_t n, uint32_t bp, uint32_t add) {
+  const uint32_t a = n / 10000u, r = n - a * 10000u;
+  return (int64_t)(a * bp + (r * bp + add) / 10000u);
+}
+
+// n < 2^31
 __host__ __device__ inline Geometry make_geometry(int64_t n, const SelParams& p) {
   Geometry g;
   g.n = n;
-  int64_t N = ceil_div64(n * p.exact_bp, 10000);
+  const uint32_t n32 = (uint32_t)n;
+  int64_t N = bp_of(n32, (uint32_t)p.exact_bp, 9999u);  // rounded up
   if (N < 1) N = 1;
   if (N > n) N = n;
-  int64_t W = ceil_div64(n * p.win_bp, 10000);
+  int64_t W = bp_of(n32, (uint32_t)p.win_bp, 9999u);
   if (W < p.win_min) W = p.win_min;
-  const int64_t c1 = (n * p.p1_bp + 5000) / 10000;
-  const int64_t c2 = (n * p.p2_bp + 5000) / 10000;
+  const int64_t c1 = bp_of(n32, (uint32_t)p.p1_bp, 5000u);
+  const int64_t c2 = bp_of(n32, (uint32_t)p.p2_bp, 5000u);
   int64_t s1 = c1 - W / 2;
   if (s1 < N + 1) s1 = N + 1;
   int64_t t1 = s1 + W - 1;

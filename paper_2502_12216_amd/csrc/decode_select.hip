@@ -127,9 +127,9 @@ __global__ __launch_bounds__(256) void score_clusters_kernel(ScoreArgs a) {
 //    ascending id.  The bucket of a score is a monotone function of it, so
 //    bucket order agrees with key order and every element's rank is its
 //    bucket start plus the number of smaller keys in its bucket.  The map
-//    squashes the standardised score z = (s - mean) / sd through
-//    z / (1 + |z|), which spreads a bell-shaped score distribution with far
-//    outliers evenly over the buckets (about one element per bucket), where a
+//    takes the standardised score z = (s - mean) / sd to log2(1 + |z|) on each
+//    side of the mean, which spreads a bell-shaped score distribution with far
+//    outliers over the buckets (at most about 1.5 times the mean load), where a
 //    linear map over [min, max] would crowd the bulk into a few buckets.  Then
 //    the tokens ahead of every rank (exclusive prefix of cluster sizes in rank
 //    order) and the rows of the sampled positions: exact head 1..N and the
@@ -142,36 +142,83 @@ __device__ __forceinline__ uint32_t desc_key_bits(float s) {
   return ~ord;
 }
 
-// Monotone non-increasing in s (NaN last).  With r = 1 / (1 + |z|) in (0, 1]
-// the bucket is (nb / 2) r for z >= 0 and nb - (nb / 2) r for z < 0, i.e.
-// (1 - u) nb for u = 1/2 + sign(z) (1 - r) / 2.  Every step is monotone in its
-// input: fp32 subtract, scale by a positive constant, absolute value, add,
-// correctly rounded divide, scale by a power of two (exact), subtract from
-// nb, truncation and clamp; the two branches meet at nb / 2.
-__device__ __forceinline__ int squash_bucket(float s, float mu, float inv_sd, int nb) {
+// Bucket of a score, monotone non-increasing in s (NaN last): with x the fp32
+// bits of 1 + |z| less those of 1 (a piecewise linear log2(1 + |z|), 2^23 per
+// octave), capped below three octaves (|z| < 7), the place on a side is
+// i = floor(x half / (3 2^23)) < half, and the bucket half - 1 - i for z >= 0, half + i
+// for z < 0.  Every step is monotone in its input: fp32 subtract, scale by a
+// positive constant, absolute value, add, the bits of a positive float, an
+// integer product with a constant.  (z / (1 + |z|), a correctly rounded
+// division, took twice the instructions; every path computes two to three
+// buckets per cluster.)
+__device__ __forceinline__ int score_bucket(float s, float mu, float inv_sd, int nb) {
   if (!(s == s)) return nb - 1;
   const float z = (s - mu) * inv_sd;
-  const float half = 0.5f * (float)nb;
-  const float x = half * (1.0f / (1.0f + fabsf(z)));  // (0, nb/2], non-increasing in |z|
-  const int bk = (int)(z >= 0.f ? x : (float)nb - x);
-  return min(max(bk, 0), nb - 1);
+  const uint32_t half = (uint32_t)nb / 2;
+  const uint32_t x = min(__float_as_uint(1.0f + fabsf(z)) - 0x3f800000u, 3u * (1u << 23) - 1u);
+  const int i = (int)__umulhi(x << 7, half * 4u / 3u);
+  return z >= 0.f ? (int)half - 1 - i : (int)half + i;
 }
 
-// Exclusive scan in place of a[0..1024 kPer) in LDS by 1024 threads, kPer
-// consecutive entries each (16-byte LDS accesses when kPer is 8); returns the
-// total.  Ends with a barrier.
+// Mean and reciprocal standard deviation of a head's scores for the bucket map,
+// and whether all C of them are equal, from each thread's sums over its
+// scores of d = s - pivot (the first score: the sums then carry the spread
+// whatever the scores' common offset): sm = sum d, sq = sum d^2, nf = scores
+// that are not NaN, diff = some d is not 0.  1024 threads, one barrier.
+__device__ __forceinline__ void score_moments(float pivot, float sm, float sq, int nf, bool diff, int C, float (*s_red)[4],
+                                              float* mu, float* inv_sd, bool* all_equal) {
+  const int wave = threadIdx.x / kWave;
+  sm = wave_allsum_f(sm);  // DPP, no LDS
+  sq = wave_allsum_f(sq);
+  const bool any = __any(diff);
+  if ((threadIdx.x & (kWave - 1)) == 0)
+    *reinterpret_cast<float4*>(s_red[wave]) = make_float4(sm, sq, (float)nf, any ? 1.f : 0.f);
+  __syncthreads();
+  // lanes 0 .. 15 of every wave take one wave's sums each
+  const float4 r = *reinterpret_cast<const float4*>(s_red[threadIdx.x & 15]);
+  sm = sum16(r.x);
+  sq = sum16(r.y);
+  const float n = sum16(r.z);
+  *all_equal = sum16(r.w) == 0.f && n == (float)C;
+  const float inv_n = 1.f / fmaxf(n, 1.f), m = sm * inv_n;
+  const float var = fmaxf(sq * inv_n - m * m, 0.f);
+  *mu = pivot + m;
+  *inv_sd = var > 0.f ? 1.f / sqrtf(var) : 1.f;
+}
+
+// A thread's kPer consecutive entries of an LDS array (from entry tid kPer),
+// in 16-byte accesses where kPer allows them.
 template <int kPer>
-__device__ uint32_t scan_lds(uint32_t* a, uint32_t* s_wave) {
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  uint32_t v[kPer];
-  if constexpr (kPer == 8) {
-    const uint4* a4 = reinterpret_cast<const uint4*>(a) + tid * 2;
-    const uint4 x = a4[0], y = a4[1];
-    v[0] = x.x, v[1] = x.y, v[2] = x.z, v[3] = x.w, v[4] = y.x, v[5] = y.y, v[6] = y.z, v[7] = y.w;
+__device__ __forceinline__ void lds_get(const uint32_t* a, uint32_t (&v)[kPer]) {
+  if constexpr (kPer % 4 == 0) {
+#pragma unroll
+    for (int e = 0; e < kPer; e += 4) {
+      const uint4 x = reinterpret_cast<const uint4*>(a)[(threadIdx.x * kPer + e) / 4];
+      v[e] = x.x, v[e + 1] = x.y, v[e + 2] = x.z, v[e + 3] = x.w;
+    }
   } else {
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) v[e] = a[tid * kPer + e];
+    for (int e = 0; e < kPer; ++e) v[e] = a[threadIdx.x * kPer + e];
   }
+}
+template <int kPer>
+__device__ __forceinline__ void lds_put(uint32_t* a, const uint32_t (&v)[kPer]) {
+  if constexpr (kPer % 4 == 0) {
+#pragma unroll
+    for (int e = 0; e < kPer; e += 4)
+      reinterpret_cast<uint4*>(a)[(threadIdx.x * kPer + e) / 4] = make_uint4(v[e], v[e + 1], v[e + 2], v[e + 3]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) a[threadIdx.x * kPer + e] = v[e];
+  }
+}
+
+// Exclusive scan of the 1024 kPer values that 1024 threads hold (kPer
+// consecutive ones each) into a[] in LDS; returns the total.  Ends with a
+// barrier.
+template <int kPer>
+__device__ uint32_t scan_regs(const uint32_t (&v)[kPer], uint32_t* a, uint32_t* s_wave) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   uint32_t local = 0;
 #pragma unroll
   for (int e = 0; e < kPer; ++e) local += v[e];
@@ -192,17 +239,18 @@ __device__ uint32_t scan_lds(uint32_t* a, uint32_t* s_wave) {
     o[e] = run;
     run += v[e];
   }
-  if constexpr (kPer == 8) {
-    uint4* a4 = reinterpret_cast<uint4*>(a) + tid * 2;
-    a4[0] = make_uint4(o[0], o[1], o[2], o[3]);
-    a4[1] = make_uint4(o[4], o[5], o[6], o[7]);
-  } else {
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) a[tid * kPer + e] = o[e];
-  }
+  lds_put<kPer>(a, o);
   const uint32_t total = s_wave[16];
   __syncthreads();
   return total;
+}
+
+// The same in place.
+template <int kPer>
+__device__ uint32_t scan_lds(uint32_t* a, uint32_t* s_wave) {
+  uint32_t v[kPer];
+  lds_get<kPer>(a, v);
+  return scan_regs<kPer>(v, a, s_wave);
 }
 __device__ __forceinline__ uint32_t scan8k_lds(uint32_t* a, uint32_t* s_wave) { return scan_lds<8>(a, s_wave); }
 
@@ -235,12 +283,15 @@ constexpr size_t kPieceLdsBytes = (size_t)kPieceBuckets * 8 + (size_t)kPieceCap 
 // starts on the general path; then the rank prefix for the sample search
 constexpr size_t kSortWsLdsBytes = kPieceLdsBytes > (size_t)kSortLdsBuckets * 8 ? kPieceLdsBytes : (size_t)kSortLdsBuckets * 8;
 
-template <bool kLds>
+// kE > 0: everything in LDS, kE clusters per thread (at most 1024 kE) and 1024 kE
+// buckets; kE = 0: the workspace paths.
+template <int kE>
 __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
+  constexpr bool kLds = kE > 0;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ uint32_t s_wave_u[17];
   __shared__ float s_wave_f[17];
-  __shared__ float s_red[16][4];
+  __shared__ __align__(16) float s_red[16][4];
   const int tid = threadIdx.x, nt = blockDim.x;
   const int bh = blockIdx.x;
   const int b = bh / a.Hq, h = bh % a.Hq, g = h / a.G;
@@ -248,10 +299,12 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
   // LDS path: the head's scores, loaded first and unconditionally at indices
   // clamped to the stride Cm (>= C; the entries past C are masked later), so
   // that they travel with the cluster-count load instead of after it
-  float raw[8];
+  float raw[kLds ? kE : 1];
+  float pivot = sc[0];  // (uniform; NaN: 0)
+  pivot = pivot == pivot ? pivot : 0.f;
   if constexpr (kLds) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) raw[e] = sc[min(tid + e * 1024, a.Cm - 1)];
+    for (int e = 0; e < kE; ++e) raw[e] = sc[min(tid + e * 1024, a.Cm - 1)];
   }
   const int64_t cb = a.cl_indptr[b];
   const int C = min((int)(a.cl_indptr[b + 1] - cb), a.Cm);
@@ -259,106 +312,91 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
   const int32_t* off = a.offsets + (int64_t)g * (a.Ct + a.B) + cb + b;
   int32_t* rank_of = a.rank_of + (int64_t)bh * a.Cm;
   int32_t* order = a.order + (int64_t)bh * a.Cm;
+  // the clusters hold the first n_c rows; the rest are recent tokens, sampled
+  // (all of them) after the exact head and the windows of the clustered list.
+  // From two uniform loads, ahead of the sort: the scalar unit works out the
+  // 64-bit geometry (after the sort, on a total read from LDS, it had taken
+  // every wave about 500 vector instructions, 1.8 us of the kernel)
+  const uint32_t listed = (uint32_t)(off[max(C, 0)] - off[0]);
+  const int n_c = (int)min((int64_t)listed, (int64_t)n);
+  const int tail = min(max(n - n_c, 0), a.max_tail);
+  const Geometry geo = make_geometry(n_c, a.prm);
+  const int64_t S_main = min(geo.samples, a.S_cap);
+  const int64_t S = min(S_main + tail, a.S_cap);
 
   uint32_t* cnt;      // per rank: cluster size, then the exclusive prefix
-  int32_t* ostart;    // per rank: first row of the cluster
+  int32_t* ostart;    // per cluster: its first row
+  int32_t* ord_s = nullptr;  // per rank: the cluster
   uint32_t total = 0; // tokens of the sequence (prefix at rank C)
   // ranks [rk_lo, rk_hi) of this workgroup, holding token positions
   // (tok_lo, tok_hi]; the whole order except when a head's pieces are shared
   int rk_lo = 0, rk_hi = -1;
   uint32_t tok_lo = 0, tok_hi = 0;
   if constexpr (kLds) {
-    // LDS: keys u64[8192] (after ranking: ostart i32[8192], ord_s i32[8192]),
-    // cnt u32[8192], start u32[8192]
+    // LDS: keys u64[nb] (after ranking: ostart i32[nb] by cluster, ord_s i32[nb]
+    // by rank),
+    // cnt u32[nb], start u32[nb]
+    constexpr int nb = kE * 1024;
     uint64_t* keys = reinterpret_cast<uint64_t*>(smem_raw);
-    cnt = reinterpret_cast<uint32_t*>(keys + kSortLdsBuckets);
-    uint32_t* start = cnt + kSortLdsBuckets;
+    cnt = reinterpret_cast<uint32_t*>(keys + nb);
+    uint32_t* start = cnt + nb;
     ostart = reinterpret_cast<int32_t*>(keys);
-    int32_t* ord_s = ostart + kSortLdsBuckets;
-    constexpr int nb = kSortLdsBuckets;
-    // every thread keeps its 8 elements in registers (C <= 8192 = 8 * 1024)
-    float v[8];
-    int o0[8], o1[8], bk[8], pos[8];
+    ord_s = ostart + nb;
+    // every thread keeps its kE elements in registers
+    float v[kE];
+    int o0[kE], o1[kE], bk[kE], pos[kE];
     // the offsets too are loaded unconditionally, at indices clamped into the
     // (b, g) list, so that all of them are in flight together (a guarded load
     // whose value is used inside its guard waits there); they are first used
     // after the ranking, so their latency hides behind the phases before it
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {  // the (b, g) list holds C + 1 entries (one when C = 0)
+    for (int e = 0; e < kE; ++e) {  // the (b, g) list holds C + 1 entries (one when C = 0)
       const int jc = max(min(tid + e * 1024, C - 1), 0);
       o0[e] = off[jc];
       o1[e] = off[min(jc + 1, C)];
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = tid + e * 1024 < C ? raw[e] : NAN;
-    {
-      uint4* c4 = reinterpret_cast<uint4*>(cnt) + tid * 2;
-      c4[0] = make_uint4(0, 0, 0, 0);
-      c4[1] = make_uint4(0, 0, 0, 0);
-    }
-    // moments and range of the finite scores (one barrier)
-    float sm = 0.f, sq = 0.f, lo = INFINITY, hi = -INFINITY, nf = 0.f;
+    for (int e = 0; e < kE; ++e) v[e] = tid + e * 1024 < C ? raw[e] : NAN;
+    uint32_t zero[kE];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      if (v[e] == v[e]) {
-        sm += v[e];
-        sq += v[e] * v[e];
-        lo = fminf(lo, v[e]);
-        hi = fmaxf(hi, v[e]);
-        nf += 1.f;
-      }
+    for (int e = 0; e < kE; ++e) zero[e] = 0u;
+    lds_put<kE>(cnt, zero);
+    float sm = 0.f, sq = 0.f, mu, inv_sd;
+    int nf = 0;  // of the wave
+    bool diff = false, all_equal;
+#pragma unroll
+    for (int e = 0; e < kE; ++e) {
+      const float d = v[e] == v[e] ? v[e] - pivot : 0.f;
+      sm += d;
+      sq = fmaf(d, d, sq);
+      diff |= d != 0.f;
+      nf += (int)__popcll(__ballot(v[e] == v[e]));
     }
-    sm = wave_allsum_f(sm);  // DPP, no LDS
-    sq = wave_allsum_f(sq);
-    nf = wave_allsum_f(nf);
-    lo = wave_allmin_f(lo);
-    hi = wave_allmax_f(hi);
-    if ((tid & (kWave - 1)) == 0) {
-      s_red[tid / kWave][0] = sm;
-      s_red[tid / kWave][1] = sq;
-      s_red[tid / kWave][2] = lo;
-      s_red[tid / kWave][3] = hi;
-      s_wave_f[tid / kWave] = nf;
-    }
-    __syncthreads();
-    sm = 0.f, sq = 0.f, lo = INFINITY, hi = -INFINITY, nf = 0.f;
-    for (int w = 0; w < 16; ++w) {
-      sm += s_red[w][0];
-      sq += s_red[w][1];
-      lo = fminf(lo, s_red[w][2]);
-      hi = fmaxf(hi, s_red[w][3]);
-      nf += s_wave_f[w];
-    }
-    if (lo == hi && nf == (float)C) {
+    score_moments(pivot, sm, sq, nf, diff, C, s_red, &mu, &inv_sd, &all_equal);
+    if (all_equal) {
       // all scores equal: the order is the cluster id
 #pragma unroll
-      for (int e = 0; e < 8; ++e) pos[e] = tid + e * 1024;
+      for (int e = 0; e < kE; ++e) pos[e] = tid + e * 1024;
     } else {
-      const float mu = nf > 0.f ? sm / nf : 0.f;
-      const float var = nf > 0.f ? fmaxf(sq / nf - mu * mu, 0.f) : 0.f;
-      const float sd = sqrtf(var);
-      const float inv_sd = sd > 0.f ? 1.f / sd : (hi > lo ? 1.f / (hi - lo) : 1.f);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        bk[e] = squash_bucket(v[e], mu, inv_sd, nb);
+      for (int e = 0; e < kE; ++e) {
+        bk[e] = score_bucket(v[e], mu, inv_sd, nb);
         if (tid + e * 1024 < C) atomicAdd(&cnt[bk[e]], 1u);
       }
       __syncthreads();
       {
-        const uint4* c4 = reinterpret_cast<const uint4*>(cnt) + tid * 2;
-        uint4* s4 = reinterpret_cast<uint4*>(start) + tid * 2;
-        s4[0] = c4[0];
-        s4[1] = c4[1];
+        uint32_t c[kE];
+        lds_get<kE>(cnt, c);
+        scan_regs<kE>(c, start, s_wave_u);
       }
-      scan8k_lds(start, s_wave_u);  // (each thread copied the entries it scans)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      for (int e = 0; e < kE; ++e) {
         const int j = tid + e * 1024;
         if (j < C) keys[atomicAdd(&start[bk[e]], 1u)] = ((uint64_t)desc_key_bits(v[e]) << 32) | (uint32_t)j;
       }
       __syncthreads();
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      for (int e = 0; e < kE; ++e) {
         const int j = tid + e * 1024;
         pos[e] = 0;
         if (j < C) {
@@ -375,36 +413,58 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
       }
       __syncthreads();
     }
-    // sizes, starts and ids by rank; ranks >= C hold size 0
-    {
-      uint4* c4 = reinterpret_cast<uint4*>(cnt) + tid * 2;
-      c4[0] = make_uint4(0, 0, 0, 0);
-      c4[1] = make_uint4(0, 0, 0, 0);
-    }
-    __syncthreads();
+    // size and id by rank in one word (ranks >= C hold size 0; ids take 13
+    // bits), the clusters' first rows by id: one scattered LDS store per
+    // cluster where three (size, first row, id) had taken 2.6 us of 8192
+    // clusters.  A cluster of 2^19 rows or more sends its head to separate
+    // arrays.
+    bool wide = false;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      if (tid + e * 1024 < C) {
-        cnt[pos[e]] = (uint32_t)(o1[e] - o0[e]);
-        ostart[pos[e]] = o0[e];
-        ord_s[pos[e]] = tid + e * 1024;
+    for (int e = 0; e < kE; ++e) wide |= tid + e * 1024 < C && (uint32_t)(o1[e] - o0[e]) >> 19 != 0;
+    lds_put<kE>(cnt, zero);
+    const bool sep = __syncthreads_or(wide);
+#pragma unroll
+    for (int e = 0; e < kE; ++e) {
+      const int j = tid + e * 1024;
+      if (j < C) {
+        const uint32_t size = (uint32_t)(o1[e] - o0[e]);
+        if (sep) {
+          cnt[pos[e]] = size;
+          ord_s[pos[e]] = j;
+        } else {
+          cnt[pos[e]] = size << 13 | (uint32_t)j;
+        }
+        ostart[j] = o0[e];
       }
     }
     __syncthreads();
-    total = scan8k_lds(cnt, s_wave_u);  // cnt has no entry C when C == 8192
+    int os[kE];  // ids of the ranks tid + 1024 e
+    uint32_t pv[kE];
+    {
+      uint32_t w[kE];
+      lds_get<kE>(cnt, w);
+      if (!sep) {
+        uint32_t id[kE];
+#pragma unroll
+        for (int e = 0; e < kE; ++e) {
+          id[e] = w[e] & 8191u;
+          w[e] >>= 13;
+        }
+        lds_put<kE>(reinterpret_cast<uint32_t*>(ord_s), id);
+      }
+      total = scan_regs<kE>(w, cnt, s_wave_u);  // cnt has no entry C when C == nb
+    }
     // global results after the last barrier (no barrier waits on these
     // stores); the LDS reads first, unconditional (every index is inside the
-    // 8192-entry arrays), so that they are in flight together
-    int os[8];
-    uint32_t pv[8];
+    // nb-entry arrays), so that they are in flight together
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < kE; ++e) {
       os[e] = ord_s[tid + e * 1024];
       pv[e] = cnt[tid + e * 1024];
     }
     int32_t* rpre = a.rprefix + (int64_t)bh * (a.Cm + 1);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < kE; ++e) {
       const int j = tid + e * 1024;
       if (j < C) {
         rank_of[j] = pos[e];
@@ -412,21 +472,21 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
       }
       if (j <= C) rpre[j] = (int32_t)(j < C ? pv[e] : total);
     }
-    if (tid == 0 && C == kSortLdsBuckets) rpre[C] = (int32_t)total;  // the one entry past the 8192
+    if (tid == 0 && C == nb) rpre[C] = (int32_t)total;  // the one entry past the nb
   } else {
     cnt = a.g_cnt + (int64_t)bh * (a.nb_max + 4);  // per rank: size, then prefix
     ostart = nullptr;                              // the sample rows start from off[order[r]]
     bool pieces_done = false;
     if (C > 0 && C <= kPieceMaxC) {  // uniform; its loads clamp indices to C - 1
-      constexpr int nbk = kPieceBuckets, kE = kPieceMaxC / 1024;
+      constexpr int nbk = kPieceBuckets, kP = kPieceMaxC / 1024;
       uint32_t* cnt_l = reinterpret_cast<uint32_t*>(smem_raw);  // bucket sizes
       uint32_t* st_l = cnt_l + nbk;                             // bucket starts
       uint64_t* s_keys = reinterpret_cast<uint64_t*>(st_l + nbk);  // the piece's keys by bucket position
       uint32_t* s_aux = reinterpret_cast<uint32_t*>(s_keys + kPieceCap);  // size by position, then rank
       int32_t* s_ord = reinterpret_cast<int32_t*>(s_aux + kPieceCap);     // cluster by rank in the piece
       uint32_t* s_sz = reinterpret_cast<uint32_t*>(s_ord + kPieceCap);    // size, then prefix, by rank
-      float v[kE];     // the score, then the rank
-      uint32_t ps[kE];  // size (low 16 bits) | place in its bucket, then bucket position (high 16 bits)
+      float v[kP];     // the score, then the rank
+      uint32_t ps[kP];  // size (low 16 bits) | place in its bucket, then bucket position (high 16 bits)
       uint32_t size_or = 0;  // OR of the sizes: any bit above 15 sends the head to the general path
       const int nv = C > tid ? (C - tid + 1023) / 1024 : 0;  // clusters of this thread: tid + 1024 e, e < nv
       // the cluster id, rebuilt at each use rather than kept in 32 registers
@@ -436,18 +496,18 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
         return t + e * 1024;
       };
 #pragma unroll
-      for (int e = 0; e < kE; ++e) v[e] = sc[min(cid(e), C - 1)];
+      for (int e = 0; e < kP; ++e) v[e] = sc[min(cid(e), C - 1)];
 #pragma unroll
-      for (int e0 = 0; e0 < kE; e0 += kE / 2) {  // sizes: 32 offset loads in flight per batch
-        int o0[kE / 2], o1[kE / 2];
+      for (int e0 = 0; e0 < kP; e0 += kP / 2) {  // sizes: 32 offset loads in flight per batch
+        int o0[kP / 2], o1[kP / 2];
 #pragma unroll
-        for (int e = 0; e < kE / 2; ++e) {
+        for (int e = 0; e < kP / 2; ++e) {
           const int jc = min(cid(e0 + e), C - 1);
           o0[e] = off[jc];
           o1[e] = off[jc + 1];
         }
 #pragma unroll
-        for (int e = 0; e < kE / 2; ++e) {
+        for (int e = 0; e < kP / 2; ++e) {
           uint32_t x = (uint32_t)(o1[e] - o0[e]);
           size_or |= x;
           // taken now, so that the loaded offsets die here
@@ -456,50 +516,27 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
         }
       }
       reinterpret_cast<uint4*>(cnt_l)[tid] = make_uint4(0, 0, 0, 0);
-      float sm = 0.f, sq = 0.f, lo = INFINITY, hi = -INFINITY, nf = 0.f;
+      float sm = 0.f, sq = 0.f, mu, inv_sd;
+      int nf = 0;  // of the wave
+      bool diff = false, all_equal;  // (all equal: the general path orders them by id)
 #pragma unroll
-      for (int e = 0; e < kE; ++e) {
-        if (e < nv && v[e] == v[e]) {
-          sm += v[e];
-          sq += v[e] * v[e];
-          lo = fminf(lo, v[e]);
-          hi = fmaxf(hi, v[e]);
-          nf += 1.f;
-        }
+      for (int e = 0; e < kP; ++e) {
+        const bool num = e < nv && v[e] == v[e];
+        const float d = num ? v[e] - pivot : 0.f;
+        sm += d;
+        sq = fmaf(d, d, sq);
+        diff |= d != 0.f;
+        nf += (int)__popcll(__ballot(num));
       }
-      sm = wave_allsum_f(sm);  // DPP, no LDS
-      sq = wave_allsum_f(sq);
-      nf = wave_allsum_f(nf);
-      lo = wave_allmin_f(lo);
-      hi = wave_allmax_f(hi);
-      if ((tid & (kWave - 1)) == 0) {
-        s_red[tid / kWave][0] = sm;
-        s_red[tid / kWave][1] = sq;
-        s_red[tid / kWave][2] = lo;
-        s_red[tid / kWave][3] = hi;
-        s_wave_f[tid / kWave] = nf;
-      }
-      __syncthreads();  // also orders the count clears before the counting below
-      sm = 0.f, sq = 0.f, lo = INFINITY, hi = -INFINITY, nf = 0.f;
-      for (int w = 0; w < 1024 / kWave; ++w) {
-        sm += s_red[w][0];
-        sq += s_red[w][1];
-        lo = fminf(lo, s_red[w][2]);
-        hi = fmaxf(hi, s_red[w][3]);
-        nf += s_wave_f[w];
-      }
-      const bool all_equal = lo == hi && nf == (float)C;  // the general path orders them by id
-      const float mu = nf > 0.f ? sm / nf : 0.f;
-      const float var = nf > 0.f ? fmaxf(sq / nf - mu * mu, 0.f) : 0.f;
-      const float sd = sqrtf(var);
-      const float inv_sd = sd > 0.f ? 1.f / sd : (hi > lo ? 1.f / (hi - lo) : 1.f);
+      // (its barrier also orders the count clears before the counting below)
+      score_moments(pivot, sm, sq, nf, diff, C, s_red, &mu, &inv_sd, &all_equal);
       if (!all_equal) {
         // counting: each cluster's place in its bucket (arrival order)
 #pragma unroll
-        for (int e0 = 0; e0 < kE; e0 += 8) {  // unconditional (adding 0 past C): 8 returns in flight
+        for (int e0 = 0; e0 < kP; e0 += 8) {  // unconditional (adding 0 past C): 8 returns in flight
 #pragma unroll
           for (int e = e0; e < e0 + 8; ++e)
-            ps[e] |= atomicAdd(&cnt_l[squash_bucket(v[e], mu, inv_sd, nbk)], e < nv ? 1u : 0u) << 16;
+            ps[e] |= atomicAdd(&cnt_l[score_bucket(v[e], mu, inv_sd, nbk)], e < nv ? 1u : 0u) << 16;
 #pragma unroll
           for (int e = e0; e < e0 + 8; ++e) asm volatile("" : "+v"(ps[e]));  // done before the next 8
         }
@@ -516,9 +553,9 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
         pieces_done = maxb <= (float)kPieceCap;
         // bucket position = bucket start + place (C <= 2^15: 16 bits)
 #pragma unroll
-        for (int e0 = 0; e0 < kE; e0 += 8) {  // 8 reads in flight
+        for (int e0 = 0; e0 < kP; e0 += 8) {  // 8 reads in flight
 #pragma unroll
-          for (int e = e0; e < e0 + 8; ++e) ps[e] += st_l[squash_bucket(v[e], mu, inv_sd, nbk)] << 16;
+          for (int e = e0; e < e0 + 8; ++e) ps[e] += st_l[score_bucket(v[e], mu, inv_sd, nbk)] << 16;
 #pragma unroll
           for (int e = e0; e < e0 + 8; ++e) asm volatile("" : "+v"(ps[e]));
         }
@@ -566,7 +603,7 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
           // tokens of the clusters ranked before r_lo, and of all clusters
           uint32_t before = 0, all = 0;
 #pragma unroll
-          for (int e = 0; e < kE; ++e) {
+          for (int e = 0; e < kP; ++e) {
             const uint32_t sz = e < nv ? (ps[e] & 0xffffu) : 0u;
             all += sz;
             before += (ps[e] >> 16) < r_lo ? sz : 0u;
@@ -613,7 +650,7 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
           for (int e = 0; e < kPiecePer; ++e) s_sz[tid * kPiecePer + e] = 0u;
           // the owners place the piece's keys and sizes at their bucket positions
 #pragma unroll
-          for (int e = 0; e < kE; ++e) {
+          for (int e = 0; e < kP; ++e) {
             const uint32_t pos = (ps[e] >> 16) - p0;
             if (e < nv && pos < len) {
               s_keys[pos] = ((uint64_t)desc_key_bits(v[e]) << 32) | (uint32_t)cid(e);
@@ -624,7 +661,7 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
           // by position: rank = bucket start + smaller keys of the bucket
           for (int t = tid; t < (int)len; t += 1024) {
             const uint64_t key = s_keys[t];
-            const int bk = squash_bucket(key_score((uint32_t)(key >> 32)), mu, inv_sd, nbk);
+            const int bk = score_bucket(key_score((uint32_t)(key >> 32)), mu, inv_sd, nbk);
             const uint32_t beg = st_l[bk] - p0, end = beg + cnt_l[bk];
             uint32_t r = beg, i = beg;
             for (; i + 4 <= end; i += 4) {  // four reads in flight
@@ -638,7 +675,7 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
           }
           __syncthreads();
 #pragma unroll
-          for (int e0 = 0; e0 < kE; e0 += 8) {  // reads at clamped positions, 8 in flight
+          for (int e0 = 0; e0 < kP; e0 += 8) {  // reads at clamped positions, 8 in flight
 #pragma unroll
             for (int e = e0; e < e0 + 8; ++e) {
               const uint32_t pos = (ps[e] >> 16) - p0;
@@ -659,7 +696,7 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
           b0 = b1;
         }
 #pragma unroll
-        for (int e = 0; e < kE; ++e) {
+        for (int e = 0; e < kP; ++e) {
           const uint32_t pos = ps[e] >> 16;
           if (e < nv && pos >= r_lo && pos < r_hi) rank_of[cid(e)] = (int32_t)__float_as_uint(v[e]);
         }
@@ -736,7 +773,7 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
           for (int e = 0; e < kB; ++e) v[e] = sc[min(j0 + e * nt, C - 1)];
 #pragma unroll
           for (int e = 0; e < kB; ++e)
-            if (j0 + e * nt < C) atomicAdd(&cnt_l[squash_bucket(v[e], mu, inv_sd, nb)], 1u);
+            if (j0 + e * nt < C) atomicAdd(&cnt_l[score_bucket(v[e], mu, inv_sd, nb)], 1u);
         }
         __syncthreads();
         {
@@ -754,7 +791,7 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
           for (int e = 0; e < kB; ++e) {
             const int j = j0 + e * nt;
             if (j < C)
-              keys[atomicAdd(&start_l[squash_bucket(v[e], mu, inv_sd, nb)], 1u)] =
+              keys[atomicAdd(&start_l[score_bucket(v[e], mu, inv_sd, nb)], 1u)] =
                   ((uint64_t)desc_key_bits(v[e]) << 32) | (uint32_t)j;
           }
         }
@@ -765,38 +802,38 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
       // bucket load together with the elements' cluster offsets; longer buckets
       // are walked after.  Then its size and first row go to its rank.
       {
-        constexpr int kE = 4, kK = 4;
-        for (int j0 = tid; j0 < C; j0 += kE * nt) {
-          uint64_t key[kE];
-          uint32_t beg[kE], end[kE], r[kE];
-          int o_lo[kE], o_hi[kE];
+        constexpr int kR = 4, kK = 4;
+        for (int j0 = tid; j0 < C; j0 += kR * nt) {
+          uint64_t key[kR];
+          uint32_t beg[kR], end[kR], r[kR];
+          int o_lo[kR], o_hi[kR];
 #pragma unroll
-          for (int e = 0; e < kE; ++e) {
+          for (int e = 0; e < kR; ++e) {
             const int jc = min(j0 + e * nt, C - 1);
             const float sv = sc[jc];
             key[e] = ((uint64_t)desc_key_bits(sv) << 32) | (uint32_t)jc;
             o_lo[e] = off[jc];
             o_hi[e] = off[jc + 1];
-            const int bk = all_equal ? 0 : squash_bucket(sv, mu, inv_sd, nb);
+            const int bk = all_equal ? 0 : score_bucket(sv, mu, inv_sd, nb);
             end[e] = all_equal ? 1u : start_l[bk];
             beg[e] = all_equal ? 0u : end[e] - cnt_l[bk];
             r[e] = 0;
           }
           if (!all_equal) {
-            uint64_t kk[kE][kK];
+            uint64_t kk[kR][kK];
 #pragma unroll
-            for (int e = 0; e < kE; ++e)
+            for (int e = 0; e < kR; ++e)
 #pragma unroll
               for (int i = 0; i < kK; ++i) kk[e][i] = keys[min(beg[e] + i, end[e] - 1)];  // the element is in it
 #pragma unroll
-            for (int e = 0; e < kE; ++e) {
+            for (int e = 0; e < kR; ++e) {
 #pragma unroll
               for (int i = 0; i < kK; ++i) r[e] += (beg[e] + i < end[e] && kk[e][i] < key[e]) ? 1u : 0u;
               for (uint32_t t = beg[e] + kK; t < end[e]; ++t) r[e] += keys[t] < key[e] ? 1u : 0u;
             }
           }
 #pragma unroll
-          for (int e = 0; e < kE; ++e) {
+          for (int e = 0; e < kR; ++e) {
             const int j = j0 + e * nt;
             if (j < C) {
               const int p2 = all_equal ? j : (int)(beg[e] + r[e]);
@@ -854,13 +891,6 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
     }
   }
 
-  // the clusters hold the first n_c rows; the rest are recent tokens, sampled
-  // (all of them) after the exact head and the windows of the clustered list
-  const int n_c = (int)min((int64_t)total, (int64_t)n);
-  const int tail = min(max(n - n_c, 0), a.max_tail);
-  const Geometry geo = make_geometry(n_c, a.prm);
-  const int64_t S_main = min(geo.samples, a.S_cap);
-  const int64_t S = min(S_main + tail, a.S_cap);
   const bool first_wg = blockIdx.y == 0;  // (more than one only when the pieces are shared)
   if (tid == 0 && first_wg) {
     int32_t* hm = a.head_meta + (int64_t)bh * 16;
@@ -985,16 +1015,16 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
     }
     return;
   }
-  // the prefix array holds the total at every rank from C to 8191 (those
-  // ranks have size 0), so steps from 4096 down never leave it and need no
+  // the prefix array holds the total at every rank from C to nb - 1 (those
+  // ranks have size 0), so steps from nb / 2 down never leave it and need no
   // clamp or end case: every entry there is >= any position searched
   int top = 1;
   while (top * 2 <= C) top <<= 1;
-  top = min(top, kSortLdsBuckets / 2);
+  top = min(top, kE * 512);
   // positions and prefixes in 32 bits (a sequence holds fewer than 2^31
-  // tokens); three searches per thread, which covers the timed shape's 2623
-  // samples in one round
-  constexpr int kU = 3;  // independent searches in flight per thread
+  // tokens); three searches per thread cover 131072 tokens' 2623 samples in
+  // one round; fewer clusters mostly come with fewer samples
+  constexpr int kU = kE >= 8 ? 3 : (kE > 1 ? 2 : 1);  // independent searches in flight per thread
   const int N32 = (int)N, NW = (int)(N + W1), s1 = (int)geo.s1, s2 = (int)geo.s2, Sm = (int)S_main;
   for (int u0 = tid; u0 < Sm; u0 += kU * nt) {
     uint32_t iv[kU];  // 1-based position in the unpacked list
@@ -1019,7 +1049,7 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
 #pragma unroll
     for (int k = 0; k < kU; ++k) {  // read together (r < C: C only with offsets that disagree with kv_indptr)
       const int r = min(lr[k], C - 1);
-      first[k] = ostart[r];
+      first[k] = ostart[ord_s[r]];
       pr[k] = cnt[r];
     }
 #pragma unroll
@@ -1984,13 +2014,22 @@ hipError_t launch_score(const ScoreArgs& a, int G, int grid_x, int grid_y, hipSt
 
 hipError_t launch_sort(const SortArgs& a, bool lds, int n_heads, hipStream_t st) {
   if (lds) {
-    const size_t bytes = (size_t)kSortLdsBuckets * 16;  // keys u64, cnt u32, start u32
-    hipLaunchKernelGGL(sort_clusters_kernel<true>, dim3(n_heads), dim3(1024), bytes, st, a);
+    // clusters per thread by the largest cluster count: every phase costs LDS
+    // and issue time per element slot, used or not (256 clusters in 8192 slots:
+    // 11.3 us)
+    const int e = a.Cm <= 1024 ? 1 : (a.Cm <= 2048 ? 2 : (a.Cm <= 4096 ? 4 : 8));
+    const size_t bytes = (size_t)e * 1024 * 16;  // keys u64, cnt u32, start u32
+    switch (e) {
+      case 1: hipLaunchKernelGGL(sort_clusters_kernel<1>, dim3(n_heads), dim3(1024), bytes, st, a); break;
+      case 2: hipLaunchKernelGGL(sort_clusters_kernel<2>, dim3(n_heads), dim3(1024), bytes, st, a); break;
+      case 4: hipLaunchKernelGGL(sort_clusters_kernel<4>, dim3(n_heads), dim3(1024), bytes, st, a); break;
+      default: hipLaunchKernelGGL(sort_clusters_kernel<8>, dim3(n_heads), dim3(1024), bytes, st, a); break;
+    }
   } else {
     // beyond 8192 clusters a head's pieces are shared by up to 8 workgroups,
     // so that few heads still occupy the device's 256 compute units
     const int nw = max(1, min(8, 256 / max(n_heads, 1)));
-    hipLaunchKernelGGL(sort_clusters_kernel<false>, dim3(n_heads, nw), dim3(1024), kSortWsLdsBytes, st, a);
+    hipLaunchKernelGGL(sort_clusters_kernel<0>, dim3(n_heads, nw), dim3(1024), kSortWsLdsBytes, st, a);
   }
   return hipGetLastError();
 }
