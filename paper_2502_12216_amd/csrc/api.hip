@@ -207,8 +207,8 @@ tactic_status tactic_sparse_decode_plan(const tactic_kv_shape* shape, const tact
   p.attn_grid = tactic::kMaxAttnGrid;
   int64_t nb = 1;
   while (nb < p.Cm) nb <<= 1;
-  p.sort_lds = nb <= tactic::kSortLdsBuckets ? 1 : 0;
-  p.nb_max = p.sort_lds ? tactic::kSortLdsBuckets : nb;
+  p.sort_lds = nb <= tactic::kSortLdsMax ? 1 : 0;
+  p.nb_max = p.sort_lds ? tactic::kSortLdsMax : nb;
 
   const int64_t BH = p.B * p.Hq, BG = p.B * p.NV;  // BG: selection groups
   Layout L;
@@ -358,7 +358,6 @@ static tactic_status sparse_decode_impl(const uint16_t* q, const uint16_t* K_sor
   fa.sample_rows = so.sample_rows;
   fa.rprefix = so.rprefix;
   fa.rank_of = so.rank_of;
-  fa.order = so.order;
   fa.logits = reinterpret_cast<double*>(ws + p.off_logit);
   fa.fit = reinterpret_cast<double*>(ws + p.off_fit);
   fa.lse = reinterpret_cast<double*>(ws + p.off_lse);

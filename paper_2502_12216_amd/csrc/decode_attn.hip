@@ -34,14 +34,25 @@ __device__ __forceinline__ int64_t group_tokens(const AttnArgs& a, int bg) {
 }
 
 // The attention splits "units" evenly over its workgroups: a group's tokens
-// plus kSegmentCost units standing for the fixed work of a group segment
-// (query load, range lookup, merge, partial store; about the time of 96
-// streamed tokens), so a workgroup that straddles groups gets fewer tokens.
-constexpr int64_t kSegmentCost = 96;
-constexpr int64_t kMinShare = 256;  // smallest split share (units) of a workgroup
+// plus a segment cost in units standing for the fixed work of a group segment
+// (query load, range lookup, merge, partial store), so a workgroup that
+// straddles groups gets fewer tokens, and a small selection, cut into shares
+// of the smallest share, mostly one segment per workgroup: a second segment
+// takes a small call as long as its first (2% of 32768 tokens, 8 groups,
+// attention: 14.4 us at 256 / 96 units, 11.7 at 64 / 32, 8.4 at 64 / 128 to
+// 256; 1M tokens 19.1 -> 17.1, 4 x 131072 at 25%: 87.4 -> 85.8 to 87.2).  Shares
+// below 64 units gain nothing and give the combine more partials.  A dense
+// share has no range lookup to spread: at least 256 units (13193 tokens, 8 KV
+// heads, with the combine: 19.8 us; 21.5 at 64, 22.7 at 192, 21.1 at 320).
+struct Split {
+  int64_t segment_cost, min_share;
+};
+__device__ __forceinline__ Split split_rule(const AttnArgs& a) {
+  return Split{192, a.dense ? 256 : 64};
+}
 __device__ __forceinline__ int64_t split_units(const AttnArgs& a, int bg) {
   const int64_t n = group_tokens(a, bg);
-  return n > 0 ? n + kSegmentCost : 0;
+  return n > 0 ? n + split_rule(a).segment_cost : 0;
 }
 
 __device__ __forceinline__ void load_words(const uint16_t* p, uint32_t* w) {
@@ -170,7 +181,7 @@ void attn_splitk_kernel(AttnArgs a) {
   const int gid = wave * GPW + grp;
   const int BG = a.B * a.NV;
 
-  // exclusive prefix of the groups' split units (tokens plus kSegmentCost for
+  // exclusive prefix of the groups' split units (tokens plus the segment cost for
   // a non-empty group): every thread sums a contiguous run of groups, then a
   // wave scan and the four wave totals
   {
@@ -192,11 +203,12 @@ void attn_splitk_kernel(AttnArgs a) {
     if (tid == 255) s_prefix[BG] = run;
     __syncthreads();
   }
+  const Split split = split_rule(a);
   const int64_t total = s_prefix[BG];
-  // a small selection is not spread thinner than kMinShare units per
+  // a small selection is not spread thinner than the smallest share per
   // workgroup: below that the fixed work of a workgroup and the partials the
   // combine must merge cost more than the extra workgroups stream
-  const int64_t share = max((total + gridDim.x - 1) / gridDim.x, kMinShare);
+  const int64_t share = max((total + gridDim.x - 1) / gridDim.x, split.min_share);
   if (blockIdx.x == 0) {  // for the combine: the split and the group offsets
     if (tid == 0) a.ameta[0] = share;
     for (int bg = tid; bg <= BG; bg += 256) a.ameta[1 + bg] = s_prefix[bg];
@@ -211,8 +223,8 @@ void attn_splitk_kernel(AttnArgs a) {
   }
 
   for (int bg = bg0; bg < BG && s_prefix[bg] < t1; ++bg) {
-    // the group's tokens follow its kSegmentCost units of setup in the split
-    const int64_t first = s_prefix[bg] + kSegmentCost;
+    // the group's tokens follow its segment cost of setup in the split
+    const int64_t first = s_prefix[bg] + split.segment_cost;
     const int64_t seg_lo = max(t0, first) - first;
     const int64_t seg_hi = min(t1, s_prefix[bg + 1]) - first;
     if (seg_lo >= seg_hi) continue;  // no token of this group in the range
@@ -555,7 +567,7 @@ __global__ __launch_bounds__(512) void combine_kernel(AttnArgs a) {
     if (slice == 0) out[d] = 0.f;
     return;
   }
-  const int64_t w0 = (P0 + kSegmentCost) / share, w1 = (P1 - 1) / share;
+  const int64_t w0 = (P0 + split_rule(a).segment_cost) / share, w1 = (P1 - 1) / share;
   const int np = (int)min(w1 - w0 + 1, (int64_t)kMaxAttnGrid);
   const float* pb = a.partials + (bg + w0) * kPart;
   const float* pd = pb + h * kHeadDim + d;  // this thread's output dimension of partial 0

@@ -7,8 +7,8 @@
 //   fit_union          per GQA group: fit y = a/x + b and the budget k of
 //                      every head, then the union of the group's selections
 //                      and the attention work list                         Sec. 4.4, 4.5, Alg. 1
-//   union_ranges       (8192 to 65536 clusters per group, up to 4 heads: the
-//                      union in slices) the slices' ranges end to end      Sec. 4.5, 4.6
+//   union_ranges       (8192 to 65536 clusters per group, 6144 to 49152 for 8
+//                      heads: the union in slices) the slices' ranges end to end      Sec. 4.5, 4.6
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(256) void score_clusters_kernel(ScoreArgs a) {
 //    the tokens ahead of every rank (exclusive prefix of cluster sizes in rank
 //    order) and the rows of the sampled positions: exact head 1..N and the
 //    two windows (Alg. 1).  One workgroup (1024 threads) per query head (up
-//    to eight per head beyond 8192 clusters, see the workspace sort below).
+//    to eight per head beyond 16384 clusters, see the workspace sort below).
 // ============================================================================
 __device__ __forceinline__ uint32_t desc_key_bits(float s) {
   const uint32_t u = __float_as_uint(s + 0.0f);  // -0 -> +0
@@ -213,26 +213,33 @@ __device__ __forceinline__ void lds_put(uint32_t* a, const uint32_t (&v)[kPer]) 
   }
 }
 
+// Exclusive scan over the 1024 threads of `local`: this thread's base; *total is
+// the sum.  Two barriers (none after the last LDS read).
+__device__ __forceinline__ uint32_t block_base(uint32_t local, uint32_t* s_wave, uint32_t* total) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const uint32_t incl = wave_incl_scan(local);  // DPP, no LDS
+  if (lane == kWave - 1) s_wave[wave] = incl;
+  __syncthreads();
+  if (wave == 0) {
+    const uint32_t w = lane < 16 ? s_wave[lane] : 0u;
+    const uint32_t wi = row_incl_scan(w);  // DPP, no LDS
+    if (lane < 16) s_wave[lane] = wi - w;
+    if (lane == 15) s_wave[16] = wi;
+  }
+  __syncthreads();
+  *total = s_wave[16];
+  return s_wave[wave] + incl - local;
+}
+
 // Exclusive scan of the 1024 kPer values that 1024 threads hold (kPer
 // consecutive ones each) into a[] in LDS; returns the total.  Ends with a
 // barrier.
 template <int kPer>
 __device__ uint32_t scan_regs(const uint32_t (&v)[kPer], uint32_t* a, uint32_t* s_wave) {
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  uint32_t local = 0;
+  uint32_t local = 0, total;
 #pragma unroll
   for (int e = 0; e < kPer; ++e) local += v[e];
-  uint32_t incl = wave_incl_scan(local);  // DPP, no LDS
-  if (lane == kWave - 1) s_wave[wave] = incl;
-  __syncthreads();
-  if (wave == 0) {
-    const uint32_t w = lane < 16 ? s_wave[lane] : 0u;
-    uint32_t wi = row_incl_scan(w);  // DPP, no LDS
-    if (lane < 16) s_wave[lane] = wi - w;
-    if (lane == 15) s_wave[16] = wi;
-  }
-  __syncthreads();
-  uint32_t run = s_wave[wave] + incl - local;
+  uint32_t run = block_base(local, s_wave, &total);
   uint32_t o[kPer];
 #pragma unroll
   for (int e = 0; e < kPer; ++e) {
@@ -240,12 +247,11 @@ __device__ uint32_t scan_regs(const uint32_t (&v)[kPer], uint32_t* a, uint32_t* 
     run += v[e];
   }
   lds_put<kPer>(a, o);
-  const uint32_t total = s_wave[16];
   __syncthreads();
   return total;
 }
 
-// The same in place.
+// scan_regs of a[] in place.
 template <int kPer>
 __device__ uint32_t scan_lds(uint32_t* a, uint32_t* s_wave) {
   uint32_t v[kPer];
@@ -260,7 +266,8 @@ __device__ __forceinline__ float key_score(uint32_t k) {
   return __uint_as_float((ord & 0x80000000u) ? (ord & 0x7fffffffu) : ~ord);
 }
 
-// Workspace sort of 8192 < C <= kPieceMaxC clusters: the scores and sizes of
+// Workspace sort of up to kPieceMaxC clusters (of a batch with more than 16384
+// per head): the scores and sizes of
 // a thread's 32 clusters stay in registers; the bucket counts (kPieceBuckets)
 // sit in LDS, and counting them gives each cluster its place in its bucket,
 // so after the scan each cluster knows its position in bucket order.  The
@@ -284,9 +291,10 @@ constexpr size_t kPieceLdsBytes = (size_t)kPieceBuckets * 8 + (size_t)kPieceCap 
 constexpr size_t kSortWsLdsBytes = kPieceLdsBytes > (size_t)kSortLdsBuckets * 8 ? kPieceLdsBytes : (size_t)kSortLdsBuckets * 8;
 
 // kE > 0: everything in LDS, kE clusters per thread (at most 1024 kE) and 1024 kE
-// buckets; kE = 0: the workspace paths.
-template <int kE>
-__global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
+// buckets; kE = 0: the workspace paths.  kCompact: 8 bytes of LDS per slot
+// instead of 16 (32-bit score keys with 16-bit ids and bucket ends).
+template <int kE, bool kCompact>
+__device__ __forceinline__ void sort_head(const SortArgs a) {
   constexpr bool kLds = kE > 0;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ uint32_t s_wave_u[17];
@@ -296,16 +304,15 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
   const int bh = blockIdx.x;
   const int b = bh / a.Hq, h = bh % a.Hq, g = h / a.G;
   const float* sc = a.scores + (int64_t)bh * a.Cm;
-  // LDS path: the head's scores, loaded first and unconditionally at indices
-  // clamped to the stride Cm (>= C; the entries past C are masked later), so
-  // that they travel with the cluster-count load instead of after it
+  // LDS path: the head's scores, unconditionally at indices clamped to the
+  // stride Cm (>= C; the entries past C are masked later)
   float raw[kLds ? kE : 1];
-  float pivot = sc[0];  // (uniform; NaN: 0)
-  pivot = pivot == pivot ? pivot : 0.f;
   if constexpr (kLds) {
 #pragma unroll
     for (int e = 0; e < kE; ++e) raw[e] = sc[min(tid + e * 1024, a.Cm - 1)];
   }
+  float pivot = sc[0];  // (uniform; NaN: 0)
+  pivot = pivot == pivot ? pivot : 0.f;
   const int64_t cb = a.cl_indptr[b];
   const int C = min((int)(a.cl_indptr[b + 1] - cb), a.Cm);
   const int n = (int)seq_tokens(a.kv_indptr, a.seq_len, b);
@@ -327,6 +334,7 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
   uint32_t* cnt;      // per rank: cluster size, then the exclusive prefix
   int32_t* ostart;    // per cluster: its first row
   int32_t* ord_s = nullptr;  // per rank: the cluster
+  uint16_t* ord16 = nullptr;  // the same, compact
   uint32_t total = 0; // tokens of the sequence (prefix at rank C)
   // ranks [rk_lo, rk_hi) of this workgroup, holding token positions
   // (tok_lo, tok_hi]; the whole order except when a head's pieces are shared
@@ -334,14 +342,21 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
   uint32_t tok_lo = 0, tok_hi = 0;
   if constexpr (kLds) {
     // LDS: keys u64[nb] (after ranking: ostart i32[nb] by cluster, ord_s i32[nb]
-    // by rank),
-    // cnt u32[nb], start u32[nb]
+    // by rank), cnt u32[nb], start u32[nb].  Compact: keys u32[nb], ids u16[nb],
+    // bucket counts, then ends, u16[nb]; after ranking cnt u32[nb] over the
+    // keys and the ids by rank over the ids.
     constexpr int nb = kE * 1024;
+    constexpr int kIdBits = kE == 16 ? 14 : 13;
     uint64_t* keys = reinterpret_cast<uint64_t*>(smem_raw);
-    cnt = reinterpret_cast<uint32_t*>(keys + nb);
+    uint32_t* keys32 = reinterpret_cast<uint32_t*>(smem_raw);
+    uint16_t* ids = reinterpret_cast<uint16_t*>(keys32 + nb);
+    uint32_t* ends = reinterpret_cast<uint32_t*>(ids + nb);  // two buckets per word
+    const uint16_t* end16 = reinterpret_cast<const uint16_t*>(ends);
+    cnt = kCompact ? keys32 : reinterpret_cast<uint32_t*>(keys + nb);
     uint32_t* start = cnt + nb;
     ostart = reinterpret_cast<int32_t*>(keys);
     ord_s = ostart + nb;
+    ord16 = ids;
     // every thread keeps its kE elements in registers
     float v[kE];
     int o0[kE], o1[kE], bk[kE], pos[kE];
@@ -360,7 +375,12 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
     uint32_t zero[kE];
 #pragma unroll
     for (int e = 0; e < kE; ++e) zero[e] = 0u;
-    lds_put<kE>(cnt, zero);
+    if constexpr (kCompact) {
+#pragma unroll
+      for (int e = 0; e < kE / 2; e += 4) reinterpret_cast<uint4*>(ends)[(tid * kE / 2 + e) / 4] = make_uint4(0, 0, 0, 0);
+    } else {
+      lds_put<kE>(cnt, zero);
+    }
     float sm = 0.f, sq = 0.f, mu, inv_sd;
     int nf = 0;  // of the wave
     bool diff = false, all_equal;
@@ -377,6 +397,71 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
       // all scores equal: the order is the cluster id
 #pragma unroll
       for (int e = 0; e < kE; ++e) pos[e] = tid + e * 1024;
+    } else if constexpr (kCompact) {
+      // counts, then starts, then (after the keys are placed) ends of the
+      // buckets, 16 bits each (at most 16384)
+#pragma unroll
+      for (int e = 0; e < kE; ++e) {
+        bk[e] = score_bucket(v[e], mu, inv_sd, nb);
+        if (tid + e * 1024 < C) atomicAdd(&ends[bk[e] >> 1], 1u << (16 * (bk[e] & 1)));
+      }
+      __syncthreads();
+      {
+        uint32_t w[kE / 2];
+#pragma unroll
+        for (int e = 0; e < kE / 2; e += 4) {
+          const uint4 x = reinterpret_cast<const uint4*>(ends)[(tid * kE / 2 + e) / 4];
+          w[e] = x.x, w[e + 1] = x.y, w[e + 2] = x.z, w[e + 3] = x.w;
+        }
+        uint32_t local = 0, all;
+#pragma unroll
+        for (int e = 0; e < kE / 2; ++e) local += (w[e] & 0xffffu) + (w[e] >> 16);
+        uint32_t run = block_base(local, s_wave_u, &all);
+#pragma unroll
+        for (int e = 0; e < kE / 2; ++e) {
+          const uint32_t lo = run, hi = run + (w[e] & 0xffffu);
+          run = hi + (w[e] >> 16);
+          w[e] = lo | hi << 16;
+        }
+#pragma unroll
+        for (int e = 0; e < kE / 2; e += 4)
+          reinterpret_cast<uint4*>(ends)[(tid * kE / 2 + e) / 4] = make_uint4(w[e], w[e + 1], w[e + 2], w[e + 3]);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < kE; ++e) {
+        const int j = tid + e * 1024, sh = 16 * (bk[e] & 1);
+        if (j < C) {
+          const uint32_t at = atomicAdd(&ends[bk[e] >> 1], 1u << sh) >> sh & 0xffffu;
+          keys32[at] = desc_key_bits(v[e]);
+          ids[at] = (uint16_t)j;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < kE; ++e) {
+        const int j = tid + e * 1024;
+        pos[e] = 0;
+        if (j < C) {
+          const uint32_t key = desc_key_bits(v[e]);
+          const uint32_t end = end16[bk[e]], beg = bk[e] > 0 ? end16[bk[e] - 1] : 0u;
+          uint32_t r = 0, eq = 0, t = beg;
+          for (; t + 1 < end; t += 2) {  // two LDS reads in flight per step
+            const uint32_t k0 = keys32[t], k1 = keys32[t + 1];
+            r += (k0 < key ? 1u : 0u) + (k1 < key ? 1u : 0u);
+            eq += (k0 == key ? 1u : 0u) + (k1 == key ? 1u : 0u);
+          }
+          if (t < end) {
+            const uint32_t k0 = keys32[t];
+            r += k0 < key ? 1u : 0u;
+            eq += k0 == key ? 1u : 0u;
+          }
+          if (eq > 1)  // equal scores besides its own: by id
+            for (t = beg; t < end; ++t) r += keys32[t] == key && ids[t] < j ? 1u : 0u;
+          pos[e] = (int)(beg + r);
+        }
+      }
+      __syncthreads();
     } else {
 #pragma unroll
       for (int e = 0; e < kE; ++e) {
@@ -413,14 +498,14 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
       }
       __syncthreads();
     }
-    // size and id by rank in one word (ranks >= C hold size 0; ids take 13
-    // bits), the clusters' first rows by id: one scattered LDS store per
-    // cluster where three (size, first row, id) had taken 2.6 us of 8192
-    // clusters.  A cluster of 2^19 rows or more sends its head to separate
-    // arrays.
+    // size and id by rank in one word (ranks >= C hold size 0; ids take kIdBits
+    // bits), the clusters' first rows by id (compact: left in memory): one
+    // scattered LDS store per cluster where three (size, first row, id) had
+    // taken 2.6 us of 8192 clusters.  A cluster of 2^(32 - kIdBits) rows or more
+    // sends its head to separate arrays.
     bool wide = false;
 #pragma unroll
-    for (int e = 0; e < kE; ++e) wide |= tid + e * 1024 < C && (uint32_t)(o1[e] - o0[e]) >> 19 != 0;
+    for (int e = 0; e < kE; ++e) wide |= tid + e * 1024 < C && (uint32_t)(o1[e] - o0[e]) >> (32 - kIdBits) != 0;
     lds_put<kE>(cnt, zero);
     const bool sep = __syncthreads_or(wide);
 #pragma unroll
@@ -430,11 +515,12 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
         const uint32_t size = (uint32_t)(o1[e] - o0[e]);
         if (sep) {
           cnt[pos[e]] = size;
-          ord_s[pos[e]] = j;
+          if constexpr (kCompact) ord16[pos[e]] = (uint16_t)j;
+          else ord_s[pos[e]] = j;
         } else {
-          cnt[pos[e]] = size << 13 | (uint32_t)j;
+          cnt[pos[e]] = size << kIdBits | (uint32_t)j;
         }
-        ostart[j] = o0[e];
+        if constexpr (!kCompact) ostart[j] = o0[e];
       }
     }
     __syncthreads();
@@ -447,10 +533,17 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
         uint32_t id[kE];
 #pragma unroll
         for (int e = 0; e < kE; ++e) {
-          id[e] = w[e] & 8191u;
-          w[e] >>= 13;
+          id[e] = w[e] & ((1u << kIdBits) - 1u);
+          w[e] >>= kIdBits;
         }
-        lds_put<kE>(reinterpret_cast<uint32_t*>(ord_s), id);
+        if constexpr (kCompact) {
+#pragma unroll
+          for (int e = 0; e < kE; e += 8)
+            reinterpret_cast<uint4*>(ord16)[(tid * kE + e) / 8] =
+                make_uint4(id[e] | id[e + 1] << 16, id[e + 2] | id[e + 3] << 16, id[e + 4] | id[e + 5] << 16, id[e + 6] | id[e + 7] << 16);
+        } else {
+          lds_put<kE>(reinterpret_cast<uint32_t*>(ord_s), id);
+        }
       }
       total = scan_regs<kE>(w, cnt, s_wave_u);  // cnt has no entry C when C == nb
     }
@@ -459,7 +552,8 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
     // nb-entry arrays), so that they are in flight together
 #pragma unroll
     for (int e = 0; e < kE; ++e) {
-      os[e] = ord_s[tid + e * 1024];
+      if constexpr (kCompact) os[e] = ord16[tid + e * 1024];
+      else os[e] = ord_s[tid + e * 1024];
       pv[e] = cnt[tid + e * 1024];
     }
     int32_t* rpre = a.rprefix + (int64_t)bh * (a.Cm + 1);
@@ -1024,7 +1118,7 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
   // positions and prefixes in 32 bits (a sequence holds fewer than 2^31
   // tokens); three searches per thread cover 131072 tokens' 2623 samples in
   // one round; fewer clusters mostly come with fewer samples
-  constexpr int kU = kE >= 8 ? 3 : (kE > 1 ? 2 : 1);  // independent searches in flight per thread
+  constexpr int kU = kE == 16 ? 6 : (kE == 8 ? 3 : (kE > 1 ? 2 : 1));  // independent searches in flight per thread
   const int N32 = (int)N, NW = (int)(N + W1), s1 = (int)geo.s1, s2 = (int)geo.s2, Sm = (int)S_main;
   for (int u0 = tid; u0 < Sm; u0 += kU * nt) {
     uint32_t iv[kU];  // 1-based position in the unpacked list
@@ -1049,7 +1143,8 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
 #pragma unroll
     for (int k = 0; k < kU; ++k) {  // read together (r < C: C only with offsets that disagree with kv_indptr)
       const int r = min(lr[k], C - 1);
-      first[k] = ostart[ord_s[r]];
+      if constexpr (kCompact) first[k] = off[ord16[r]];
+      else first[k] = ostart[ord_s[r]];
       pr[k] = cnt[r];
     }
 #pragma unroll
@@ -1060,16 +1155,43 @@ __global__ __launch_bounds__(1024) void sort_clusters_kernel(SortArgs a) {
   }
 }
 
+// kMax > 0: a batch of up to 1024 kMax clusters per head.  kTwo (kMax = 8): two
+// workgroups per compute unit, for more heads than compute units: compact
+// slots and half the registers (8192 slots: 24.0 against 19.4 us when every
+// head has a compute unit of its own), and each head runs with the fewest slots
+// that hold its own clusters (512 heads of 1024 to 8000 clusters: 32.5 -> 25.8
+// us).  kMax = 16 needs the compact slots for its LDS (9376 clusters x 64 heads:
+// 27.3 us, 64.0 in pieces of the workspace sort).
+template <int kMax, bool kTwo>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kTwo ? 8 : 4)))
+void sort_clusters_kernel(SortArgs a) {
+  if constexpr (kTwo || kMax == 2 || kMax == 4) {
+    const int b = blockIdx.x / a.Hq;
+    const int C = (int)(a.cl_indptr[b + 1] - a.cl_indptr[b]);
+    if (C <= 1024) return sort_head<1, false>(a);
+    if (kMax > 2 && C <= 2048) return sort_head<2, false>(a);
+    if (kMax > 4 && C <= 4096) return sort_head<4, false>(a);
+  }
+  sort_head<kMax, kTwo || kMax == 16>(a);
+}
+
 // ============================================================================
 // 3. Sampled logits, fit, cutoff, union.
 // ============================================================================
-__device__ double harmonic(int64_t x) {
-  if (x <= 0) return 0.0;
-  if (x < 64) {
-    double s = 0.0;
-    for (int64_t i = 1; i <= x; ++i) s += 1.0 / (double)i;
-    return s;
+// H(x) for x < 64, summed in ascending order
+struct HarmonicTable {
+  double h[64];
+  constexpr HarmonicTable() : h() {
+    h[0] = 0.0;
+    for (int i = 1; i < 64; ++i) h[i] = h[i - 1] + 1.0 / (double)i;
   }
+};
+__constant__ constexpr HarmonicTable kHarmonic{};
+
+// (the sum as a loop of up to 63 dependent fp64 divisions had taken 3 us of the
+// fit of a 4096-token list, whose exact head ends at 41)
+__device__ double harmonic(int64_t x) {
+  if (x < 64) return kHarmonic.h[max(x, (int64_t)0)];
   const double X = (double)x, r = 1.0 / X, r2 = r * r;
   // Euler-Maclaurin expansion of H(x) = psi(x + 1) + gamma
   return log(X) + 0.57721566490153286061 + 0.5 * r -
@@ -1456,23 +1578,24 @@ __device__ void fit_head_wave(const FitArgs& a, int bh, int lane, int* cut, bool
 
 // 3b. Fit of the G heads of a group (one wave each), then the union of their
 //     selections (Sec. 4.5) and the attention work list.  grid B*Hkv, 1024
-//     threads (the first G waves fit).  Staged form (G <= 4, Cm <= 8192):
-//     while the first G waves fit, the other waves copy the heads' cluster
-//     ranks (u16) and the cluster offsets to LDS; then every thread takes 8
-//     consecutive clusters and keeps their union lengths and offsets in
-//     registers through the scan and the range list.  Up to 65536 clusters
-//     the staged form runs in slices (grid B*Hkv x slices) and
-//     union_ranges_kernel writes the ranges.  Otherwise (G = 8), up to
-//     32768 clusters: offsets to LDS while the fit runs, the heads' first
-//     cut-rank clusters marked there from the sort order, 32-cluster segments
-//     per thread through the scan; beyond that the union lengths go through
-//     the output array between the passes.
+//     threads (the first G waves fit).  Staged form (up to 8192 clusters, 6144 for
+//     G = 8): while the first G waves fit, the other waves copy the heads'
+//     cluster ranks (u16) and the cluster offsets to LDS; then every thread
+//     takes 8 consecutive clusters and keeps their union lengths and offsets
+//     in registers through the scan and the range list.  Up to 8 times as many
+//     clusters the staged form runs in slices (grid B*Hkv x slices) and
+//     union_ranges_kernel writes the ranges.  (G = 8 had taken one workgroup
+//     per group for all clusters: 3126 clusters 20.4 us, now 13.2; 32768: 34.4 us,
+//     now 17.1 + 7.4 in eight slices.)  Beyond that the union lengths go
+//     through the output array between the passes.
 constexpr int kUnionSeg = 8;              // clusters per thread in the staged union
 constexpr int kUnionStagedMax = 8 * 1024;  // clusters of one workgroup of the staged union (kUnionSeg per thread)
+// clusters per workgroup: their LDS is 2 G + 8 bytes each, of 160 KB
+__host__ __device__ constexpr int union_stage_max(int G) { return G <= 4 ? kUnionStagedMax : 6 * 1024; }
 __host__ __device__ inline bool union_staged(int G, int64_t Cm) {
-  return G <= 4 && Cm <= (int64_t)kUnionStagedMax * kMaxUnionSlices;
+  return Cm <= (int64_t)union_stage_max(G) * kMaxUnionSlices;
 }
-__host__ __device__ inline bool union_sliced(int G, int64_t Cm) { return union_staged(G, Cm) && Cm > kUnionStagedMax; }
+__host__ __device__ inline bool union_sliced(int G, int64_t Cm) { return union_staged(G, Cm) && Cm > union_stage_max(G); }
 
 // The group's range list ends with the recent tokens (rows n_c .. n_c + tail
 // - 1, the same for every head of the group) as one more range; then the
@@ -1527,7 +1650,7 @@ __global__ __launch_bounds__(1024) void fit_union_kernel(FitArgs a) {
     // workgroup fits the group's heads, stages and measures its own slice,
     // and leaves the slice's union lengths and (ranges, tokens) total, and
     // union_ranges_kernel lays the slices' ranges end to end
-    const bool sliced = a.Cm > kUnionStagedMax;
+    const bool sliced = a.Cm > union_stage_max(G);
     const int kw = sliced ? (int)blockIdx.y : 0;
     const int Cp = sliced ? a.union_slice : (a.Cm + kUnionSeg - 1) / kUnionSeg * kUnionSeg;
     const int jb = kw * Cp, ns = sliced ? max(0, min(C - jb, Cp)) : C;  // clusters jb .. jb + ns - 1
@@ -1538,27 +1661,33 @@ __global__ __launch_bounds__(1024) void fit_union_kernel(FitArgs a) {
       fit_head_wave(a, h0 + wave, lane, s_cut[wave], kw == 0);
     } else {
       const int32_t* off = a.offsets + (int64_t)kvh * (a.Ct + a.B) + cb + b + jb;
-      // all loads of a thread are issued before its LDS stores
-      constexpr int nw = 1024 - G * kWave;
-      constexpr int kW = (kUnionStagedMax + nw) / nw;  // covers j in [0, ns] for ns <= kUnionStagedMax
+      // a thread's loads are issued before its LDS stores, four heads at a time
+      constexpr int nw = 1024 - G * kWave, kStage = union_stage_max(G);
+      constexpr int kW = (kStage + nw) / nw;  // covers j in [0, ns] for ns <= kStage
+      constexpr int kH = G < 4 ? G : 4;
       const int w = tid - G * kWave;
       int32_t ov[kW];
 #pragma unroll
       for (int i = 0; i < kW; ++i) ov[i] = w + i * nw <= ns ? off[w + i * nw] : 0;
-      int32_t rv[G][kW];
 #pragma unroll
-      for (int hh = 0; hh < G; ++hh)
+      for (int hb = 0; hb < G; hb += kH) {
+        int32_t rv[kH][kW];
 #pragma unroll
-        for (int i = 0; i < kW; ++i)
-          rv[hh][i] = w + i * nw < ns ? a.rank_of[(int64_t)(h0 + hh) * a.Cm + jb + w + i * nw] : 0;
+        for (int hh = 0; hh < kH; ++hh)
 #pragma unroll
-      for (int i = 0; i < kW; ++i)
-        if (w + i * nw <= ns) s_off[w + i * nw] = ov[i];
+          for (int i = 0; i < kW; ++i)
+            rv[hh][i] = w + i * nw < ns ? a.rank_of[(int64_t)(h0 + hb + hh) * a.Cm + jb + w + i * nw] : 0;
+        if (hb == 0) {
 #pragma unroll
-      for (int hh = 0; hh < G; ++hh)
+          for (int i = 0; i < kW; ++i)
+            if (w + i * nw <= ns) s_off[w + i * nw] = ov[i];
+        }
 #pragma unroll
-        for (int i = 0; i < kW; ++i)
-          if (w + i * nw < ns) s_rk[hh * Cp + w + i * nw] = (uint16_t)rv[hh][i];
+        for (int hh = 0; hh < kH; ++hh)
+#pragma unroll
+          for (int i = 0; i < kW; ++i)
+            if (w + i * nw < ns) s_rk[(hb + hh) * Cp + w + i * nw] = (uint16_t)rv[hh][i];
+      }
     }
     __syncthreads();
     int32_t* ulen = a.union_len + (int64_t)jg * a.Ct + cb + jb;
@@ -1666,270 +1795,70 @@ __global__ __launch_bounds__(1024) void fit_union_kernel(FitArgs a) {
     return s_wave_u[wave] + incl - loc;
   };
 
-  if (a.Cm <= kUnionLdsMax) {
-    // One workgroup per group runs every pass here, so the passes are kept
-    // short in instructions per cluster. LDS holds the cluster offsets (one
-    // pad entry after every 32, so that the threads' 32-entry segments start
-    // in different banks), their top bit set for clusters some head takes
-    // whole; later each cluster's union length or position. With many
-    // ranges: per 32 clusters a bit per non-empty cluster and the count of
-    // non-empty clusters before them.
-    static_assert(kUnionLdsMax <= 32 * 1024, "one 32-cluster segment per thread");
-    const int Cp = (a.Cm + 31) / 32 * 32;                      // whole segments
-    int32_t* const Lo = reinterpret_cast<int32_t*>(smem_raw);  // [Cp + Cp / 32 + 1]
-    auto li = [](int j) { return j + (j >> 5); };
-    uint32_t* s_nz = reinterpret_cast<uint32_t*>(Lo + Cp + Cp / 32 + 1);  // [Cp / 32]
-    int32_t* s_wb = reinterpret_cast<int32_t*>(s_nz + Cp / 32);           // [Cp / 32]
-    __shared__ int s_cutj[G];                                                  // cut cluster, -1: none
-    if (wave < G) {
-      fit_head_wave(a, h0 + wave, lane, s_cut[wave], true);
-      if (lane == 0) s_cutj[wave] = -1;
-    } else {
-      // offsets 0 .. C into LDS while the fit runs (8 per thread and step loaded together)
-      constexpr int nw = 1024 - G * kWave;
-      const int w = tid - G * kWave;
-      for (int k0 = 0; k0 * nw <= C; k0 += 8) {
-        int o[8];
+  if (wave < G) fit_head_wave(a, h0 + wave, lane, s_cut[wave], true);
+  __syncthreads();
+  // pass 1 (coalesced, kB clusters per thread and step loaded together at
+  // clamped indices): selected prefix length of every cluster = max over
+  // heads, into the union-length output
+  constexpr int kB = G >= 8 ? 4 : 8;
+  for (int k0 = 0; k0 * nt < C; k0 += kB) {
+    int o0[kB], o1[kB], rk[kB][G];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = off[min((k0 + e) * nw + w, C)];
+    for (int e = 0; e < kB; ++e) {
+      const int jj = min((k0 + e) * nt + tid, C - 1);
+      o0[e] = off[jj];
+      o1[e] = off[jj + 1];
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if ((k0 + e) * nw + w <= C) Lo[li((k0 + e) * nw + w)] = o[e];
-      }
+      for (int hh = 0; hh < G; ++hh) rk[e][hh] = a.rank_of[(int64_t)(h0 + hh) * a.Cm + jj];
     }
-    __syncthreads();
-    {
-      // marks: every head's clusters ranked before its cut (its first
-      // cut-rank entries of the sort order) get the top bit, and the cut
-      // cluster is noted; the heads' entries taken as one list, 8 per thread
-      // and step loaded together
-      int pre[G + 1];
-      pre[0] = 0;
+#pragma unroll
+    for (int e = 0; e < kB; ++e) {
+      const int j = (k0 + e) * nt + tid;
+      const int size = o1[e] - o0[e];
+      int L = 0;
 #pragma unroll
       for (int hh = 0; hh < G; ++hh) {
-        const int c0 = s_cut[hh][0];
-        pre[hh + 1] = pre[hh] + (c0 < C ? c0 + 1 : C);  // c0 = -1: no cluster
+        const int r = rk[e][hh];
+        L = max(L, r < s_cut[hh][0] ? size : (r == s_cut[hh][0] ? s_cut[hh][1] : 0));
       }
-      const int NR = pre[G];
-      auto head_of = [&](int t) {
-        int hh = 0;
-#pragma unroll
-        for (int k = 1; k < G; ++k) hh += t >= pre[k] ? 1 : 0;
-        return hh;
-      };
-      for (int t0 = 0; t0 < NR; t0 += 8 * nt) {
-        int jv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int t = min(t0 + e * nt + tid, NR - 1);
-          const int hh = head_of(t);
-          jv[e] = a.order[(int64_t)(h0 + hh) * a.Cm + (t - pre[hh])];
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int t = t0 + e * nt + tid;
-          if (t < NR) {
-            const int hh = head_of(t);
-            if (t - pre[hh] == s_cut[hh][0]) s_cutj[hh] = jv[e];
-            else atomicOr(reinterpret_cast<unsigned int*>(Lo) + li(jv[e]), 0x80000000u);
-          }
-        }
-      }
+      if (j < C) ulen[j] = L;
     }
-    __syncthreads();
-    // segments of 32 clusters (C <= 32 * 1024): union length = the size for
-    // a marked cluster, at least the cut length at a head's cut cluster
-    constexpr int kSeg = 32;
-    const int beg = tid * kSeg;
-    int L[kSeg];
-    uint64_t loc = 0;  // (ranges << 32) | tokens
-    if (beg < C) {
-      int o[kSeg + 1];
+  }
+  __syncthreads();
+  // pass 2: compact the non-empty clusters into ranges (contiguous segment
+  // per thread), 8 entries per step read together
+  const int seg = (C + nt - 1) / nt;
+  const int beg = min(C, tid * seg), end = min(C, beg + seg);
+  uint64_t loc = 0;  // (ranges << 32) | tokens
+  for (int j0 = beg; j0 < end; j0 += 8) {
+    int Lv[8];
 #pragma unroll
-      for (int e = 0; e <= kSeg; ++e) o[e] = Lo[li(min(beg + e, C))];
+    for (int e = 0; e < 8; ++e) Lv[e] = ulen[min(j0 + e, end - 1)];
 #pragma unroll
-      for (int e = 0; e < kSeg; ++e) {
-        L[e] = (o[e] < 0 && beg + e < C) ? (o[e + 1] & 0x7fffffff) - (o[e] & 0x7fffffff) : 0;
-        loc += L[e];
-      }
-      bool has_cut = false;
+    for (int e = 0; e < 8; ++e)
+      if (j0 + e < end && Lv[e] > 0) loc += (1ull << 32) | (uint64_t)Lv[e];
+  }
+  const uint64_t base = block_scan(loc);
+  // the thread writes its own segment's ranges, 8 lengths and cluster
+  // starts per step loaded together (union positions fit 32 bits: a
+  // sequence holds fewer than 2^31 tokens)
+  int idx = (int)(base >> 32), upos = (int)(base & 0xffffffffu);
+  for (int j0 = beg; j0 < end; j0 += 8) {
+    int Lv[8], ov[8];
 #pragma unroll
-      for (int hh = 0; hh < G; ++hh) has_cut |= (unsigned)(s_cutj[hh] - beg) < (unsigned)kSeg;
-      if (has_cut) {
-        loc = 0;
-#pragma unroll
-        for (int hh = 0; hh < G; ++hh) {
-          const int cj = s_cutj[hh], cl = s_cut[hh][1];
-#pragma unroll
-          for (int e = 0; e < kSeg; ++e)
-            if (beg + e == cj) L[e] = max(L[e], cl);
-        }
-#pragma unroll
-        for (int e = 0; e < kSeg; ++e) loc += L[e];
-      }
-      int nr = 0;
-#pragma unroll
-      for (int e = 0; e < kSeg; ++e) nr += L[e] > 0 ? 1 : 0;
-      loc |= (uint64_t)nr << 32;
+    for (int e = 0; e < 8; ++e) {
+      const int jj = min(j0 + e, end - 1);
+      Lv[e] = ulen[jj];
+      ov[e] = off[jj];
     }
-    const uint64_t base = block_scan(loc);
-    // few ranges (the common case with this many clusters): each thread
-    // writes its segment's ranges, scattered across the lanes but rare;
-    // else a coalesced pass writes them, neighbouring lanes writing
-    // neighbouring ranges
-    const bool few = (tot >> 32) * 8 <= (uint64_t)C;
-    if (beg < C) {
-      int idx = (int)(base >> 32), upos = (int)(base & 0xffffffffu);
-      if (few) {
-        // each cluster's union length replaces its offset (the last segment
-        // also writes entries past C, which nothing reads); a non-empty
-        // cluster's range and the position -> range index, one entry per
-        // kCfrTokens positions
 #pragma unroll
-        for (int e0 = 0; e0 < kSeg; e0 += 8) {
-          int o[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = Lo[li(beg + e0 + e)];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int Le = L[e0 + e];
-            Lo[li(beg + e0 + e)] = Le;
-            if (Le > 0) {
-              rstart[idx] = o[e] & 0x7fffffff;
-              rupos[idx] = upos;
-              for (int c = (upos + Ti - 1) / Ti; c * Ti < upos + Le && c < mc; ++c) cfr[c] = idx;
-              ++idx;
-            }
-            upos += Le;
-          }
-        }
-      } else {
-        // each cluster's union position replaces its offset (the last
-        // segment writes C's entry, the total, and entries past it, which
-        // nothing reads); the segment's non-empty bits and the range count
-        // before it
-        uint32_t nzb = 0;
-#pragma unroll
-        for (int e = 0; e < kSeg; ++e) {
-          Lo[li(beg + e)] = upos;
-          upos += L[e];
-          nzb |= (L[e] > 0 ? 1u : 0u) << e;
-        }
-        s_nz[tid] = nzb;
-        s_wb[tid] = idx;
-      }
-    }
-    if (!few && tid == 0 && (C & 31) == 0) Lo[li(C)] = (int)(tot & 0xffffffffu);  // no segment holds C
-    __syncthreads();
-    if (few) {
-      // union lengths out (coalesced)
-      for (int k0 = 0; k0 * nt < C; k0 += 8) {
-        int v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = Lo[li(min((k0 + e) * nt + tid, C - 1))];
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if ((k0 + e) * nt + tid < C) ulen[(k0 + e) * nt + tid] = v[e];
-      }
-    } else {
-      // coalesced: union lengths out, and per non-empty cluster its range
-      // (index = non-empty clusters before it) and the position -> range
-      // index; the cluster starts are loaded with the step's LDS reads, so
-      // that no load waits behind the stores
-      for (int k0 = 0; k0 * nt < C; k0 += 4) {
-        int u0[4], u1[4], wb[4], ov[4];
-        uint32_t m[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int jj = min((k0 + e) * nt + tid, C - 1);
-          ov[e] = off[jj];
-          u0[e] = Lo[li(jj)];
-          u1[e] = Lo[li(jj + 1)];
-          m[e] = s_nz[jj >> 5];
-          wb[e] = s_wb[jj >> 5];
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j = (k0 + e) * nt + tid;
-          const int Lj = u1[e] - u0[e];
-          if (j < C) {
-            ulen[j] = Lj;
-            if (Lj > 0) {
-              const int r = wb[e] + __popc(m[e] & ((1u << (j & 31)) - 1u));
-              rstart[r] = ov[e];
-              rupos[r] = u0[e];
-              for (int c = (u0[e] + Ti - 1) / Ti; c * Ti < u0[e] + Lj && c < mc; ++c) cfr[c] = r;
-            }
-          }
-        }
-      }
-    }
-  } else {
-    if (wave < G) fit_head_wave(a, h0 + wave, lane, s_cut[wave], true);
-    __syncthreads();
-    // pass 1 (coalesced, kB clusters per thread and step loaded together at
-    // clamped indices): selected prefix length of every cluster = max over
-    // heads, into the union-length output
-    constexpr int kB = G >= 8 ? 4 : 8;
-    for (int k0 = 0; k0 * nt < C; k0 += kB) {
-      int o0[kB], o1[kB], rk[kB][G];
-#pragma unroll
-      for (int e = 0; e < kB; ++e) {
-        const int jj = min((k0 + e) * nt + tid, C - 1);
-        o0[e] = off[jj];
-        o1[e] = off[jj + 1];
-#pragma unroll
-        for (int hh = 0; hh < G; ++hh) rk[e][hh] = a.rank_of[(int64_t)(h0 + hh) * a.Cm + jj];
-      }
-#pragma unroll
-      for (int e = 0; e < kB; ++e) {
-        const int j = (k0 + e) * nt + tid;
-        const int size = o1[e] - o0[e];
-        int L = 0;
-#pragma unroll
-        for (int hh = 0; hh < G; ++hh) {
-          const int r = rk[e][hh];
-          L = max(L, r < s_cut[hh][0] ? size : (r == s_cut[hh][0] ? s_cut[hh][1] : 0));
-        }
-        if (j < C) ulen[j] = L;
-      }
-    }
-    __syncthreads();
-    // pass 2: compact the non-empty clusters into ranges (contiguous segment
-    // per thread), 8 entries per step read together
-    const int seg = (C + nt - 1) / nt;
-    const int beg = min(C, tid * seg), end = min(C, beg + seg);
-    uint64_t loc = 0;  // (ranges << 32) | tokens
-    for (int j0 = beg; j0 < end; j0 += 8) {
-      int Lv[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) Lv[e] = ulen[min(j0 + e, end - 1)];
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (j0 + e < end && Lv[e] > 0) loc += (1ull << 32) | (uint64_t)Lv[e];
-    }
-    const uint64_t base = block_scan(loc);
-    // the thread writes its own segment's ranges, 8 lengths and cluster
-    // starts per step loaded together (union positions fit 32 bits: a
-    // sequence holds fewer than 2^31 tokens)
-    int idx = (int)(base >> 32), upos = (int)(base & 0xffffffffu);
-    for (int j0 = beg; j0 < end; j0 += 8) {
-      int Lv[8], ov[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int jj = min(j0 + e, end - 1);
-        Lv[e] = ulen[jj];
-        ov[e] = off[jj];
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        if (j0 + e < end && Lv[e] > 0) {
-          rstart[idx] = ov[e];
-          rupos[idx] = upos;
-          for (int c = (upos + Ti - 1) / Ti; c * Ti < upos + Lv[e] && c < mc; ++c) cfr[c] = idx;
-          ++idx;
-          upos += Lv[e];
-        }
+    for (int e = 0; e < 8; ++e) {
+      if (j0 + e < end && Lv[e] > 0) {
+        rstart[idx] = ov[e];
+        rupos[idx] = upos;
+        for (int c = (upos + Ti - 1) / Ti; c * Ti < upos + Lv[e] && c < mc; ++c) cfr[c] = idx;
+        ++idx;
+        upos += Lv[e];
       }
     }
   }
@@ -2017,19 +1946,25 @@ hipError_t launch_sort(const SortArgs& a, bool lds, int n_heads, hipStream_t st)
     // clusters per thread by the largest cluster count: every phase costs LDS
     // and issue time per element slot, used or not (256 clusters in 8192 slots:
     // 11.3 us)
-    const int e = a.Cm <= 1024 ? 1 : (a.Cm <= 2048 ? 2 : (a.Cm <= 4096 ? 4 : 8));
-    const size_t bytes = (size_t)e * 1024 * 16;  // keys u64, cnt u32, start u32
+    const int e = a.Cm <= 1024 ? 1 : (a.Cm <= 2048 ? 2 : (a.Cm <= 4096 ? 4 : (a.Cm <= 8192 ? 8 : 16)));
+    const bool two = e == 8 && n_heads > 256;
+    const size_t bytes = (size_t)e * 1024 * (two || e == 16 ? 8 : 16);
+    const dim3 grid(n_heads), block(1024);
     switch (e) {
-      case 1: hipLaunchKernelGGL(sort_clusters_kernel<1>, dim3(n_heads), dim3(1024), bytes, st, a); break;
-      case 2: hipLaunchKernelGGL(sort_clusters_kernel<2>, dim3(n_heads), dim3(1024), bytes, st, a); break;
-      case 4: hipLaunchKernelGGL(sort_clusters_kernel<4>, dim3(n_heads), dim3(1024), bytes, st, a); break;
-      default: hipLaunchKernelGGL(sort_clusters_kernel<8>, dim3(n_heads), dim3(1024), bytes, st, a); break;
+      case 1: hipLaunchKernelGGL((sort_clusters_kernel<1, false>), grid, block, bytes, st, a); break;
+      case 2: hipLaunchKernelGGL((sort_clusters_kernel<2, false>), grid, block, bytes, st, a); break;
+      case 4: hipLaunchKernelGGL((sort_clusters_kernel<4, false>), grid, block, bytes, st, a); break;
+      case 8:
+        if (two) hipLaunchKernelGGL((sort_clusters_kernel<8, true>), grid, block, bytes, st, a);
+        else hipLaunchKernelGGL((sort_clusters_kernel<8, false>), grid, block, bytes, st, a);
+        break;
+      default: hipLaunchKernelGGL((sort_clusters_kernel<16, false>), grid, block, bytes, st, a); break;
     }
   } else {
-    // beyond 8192 clusters a head's pieces are shared by up to 8 workgroups,
+    // beyond 16384 clusters a head's pieces are shared by up to 8 workgroups,
     // so that few heads still occupy the device's 256 compute units
     const int nw = max(1, min(8, 256 / max(n_heads, 1)));
-    hipLaunchKernelGGL(sort_clusters_kernel<0>, dim3(n_heads, nw), dim3(1024), kSortWsLdsBytes, st, a);
+    hipLaunchKernelGGL((sort_clusters_kernel<0, false>), dim3(n_heads, nw), dim3(1024), kSortWsLdsBytes, st, a);
   }
   return hipGetLastError();
 }
@@ -2043,22 +1978,21 @@ hipError_t launch_sample(const FitArgs& a, int split, int n_heads, bool paged, h
 hipError_t launch_fit_union(const FitArgs& args, int G, int n_groups, hipStream_t st) {
   FitArgs a = args;
   const bool sliced = union_sliced(G, a.Cm);
-  // beyond kUnionStagedMax clusters the staged union runs in slices of at
+  // beyond union_stage_max clusters the staged union runs in slices of at
   // most that many, up to kMaxUnionSlices workgroups per group (as many as
   // fill the device's 256 compute units), then a second kernel lays out the
   // ranges
   int nwu = 1;
   a.union_slice = 0;
   if (sliced) {
-    nwu = (int)max((a.Cm + kUnionStagedMax - 1) / kUnionStagedMax, (int64_t)min(kMaxUnionSlices, 256 / max(n_groups, 1)));
+    const int stage = union_stage_max(G);
+    nwu = (int)max((a.Cm + stage - 1) / stage, (int64_t)min(kMaxUnionSlices, 256 / max(n_groups, 1)));
     nwu = min(nwu, kMaxUnionSlices);
     a.union_slice = (int)(((a.Cm + nwu - 1) / nwu + kUnionSeg - 1) / kUnionSeg * kUnionSeg);
     nwu = (int)((a.Cm + a.union_slice - 1) / a.union_slice);
   }
   const int64_t Cp = sliced ? a.union_slice : (a.Cm + kUnionSeg - 1) / kUnionSeg * kUnionSeg;
-  const int64_t C32 = (a.Cm + 31) / 32 * 32;
-  const size_t lds = union_staged(G, a.Cm) ? (size_t)(G * Cp * 2 + (Cp + 4) * 4 + Cp * 4)
-                                           : (a.Cm <= kUnionLdsMax ? (size_t)(C32 + 3 * (C32 / 32) + 1) * 4 : 0);
+  const size_t lds = union_staged(G, a.Cm) ? (size_t)(G * Cp * 2 + (Cp + 4) * 4 + Cp * 4) : 0;
   const dim3 grid(n_groups, nwu);
   switch (G) {
     case 1: hipLaunchKernelGGL(fit_union_kernel<1>, grid, dim3(1024), lds, st, a); break;

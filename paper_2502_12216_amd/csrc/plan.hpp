@@ -13,11 +13,11 @@ constexpr int kTile = 64;              // tokens per attention tile
 constexpr int kMaxChunkTokens = 2048;  // tokens whose rows the attention stages in LDS at once
 constexpr int kCfrTokens = 256;        // granularity of the union's position -> range index
 constexpr int kMaxAttnGrid = 4096;     // attention workgroups the partials are sized for (cap)
-constexpr int kSortLdsBuckets = 8192;  // largest cluster count sorted in LDS
+constexpr int kSortLdsMax = 16384;     // largest cluster count sorted in LDS
+constexpr int kSortLdsBuckets = 8192;  // buckets of the general workspace sort
 constexpr int kMaxGroups = 4096;       // B * Hkv limit of the attention work list
 constexpr int kFitFields = 16;
 constexpr int kStageEvents = 7;        // start + after each of the six decode kernels
-constexpr int kUnionLdsMax = 32768;     // clusters whose union lengths are staged in LDS
 constexpr int kMaxUnionSlices = 8;    // workgroups per selection group of the sliced union
 constexpr int kScoreRows = 64;         // centroids per scoring workgroup (4096 workgroups at 8192 x 32)
 #ifndef TACTIC_SAMPLE_CHUNK
