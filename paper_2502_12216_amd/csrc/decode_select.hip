@@ -160,6 +160,11 @@ __device__ __forceinline__ int score_bucket(float s, float mu, float inv_sd, int
   return z >= 0.f ? (int)half - 1 - i : (int)half + i;
 }
 
+// Sum of a wave total per wave of 1024 threads, in every lane (a scalar).
+__device__ __forceinline__ uint32_t sum_of_waves(const uint32_t* s) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)row_incl_scan(s[threadIdx.x & 15]), 15);
+}
+
 // Mean and reciprocal standard deviation of a head's scores for the bucket map,
 // and whether all C of them are equal, from each thread's sums over its
 // scores of d = s - pivot (the first score: the sums then carry the spread
@@ -267,25 +272,28 @@ __device__ __forceinline__ float key_score(uint32_t k) {
 }
 
 // Workspace sort of up to kPieceMaxC clusters (of a batch with more than 16384
-// per head): the scores and sizes of
-// a thread's 32 clusters stay in registers; the bucket counts (kPieceBuckets)
-// sit in LDS, and counting them gives each cluster its place in its bucket,
-// so after the scan each cluster knows its position in bucket order.  The
-// buckets are then taken in pieces of consecutive buckets holding at most
-// kPieceCap clusters, whose keys are staged in LDS at those positions: every
-// access of the rank computation is an LDS access, and the global accesses
-// are coalesced.  A piece's ranks are consecutive, so its order, rank-prefix
-// and size entries leave in order.  A head's buckets are shared by the
-// workgroups of its grid column (blockIdx.y): each counts every cluster (the
-// bucket starts must be known everywhere), then ranks only the pieces of its
-// own run of whole buckets, its prefix starting at the tokens of the
-// clusters before them, and finds the sampled rows that fall in its ranks.
-// The workgroups exchange nothing; the first one also writes the head record.
+// per head): the scores, sizes and buckets of a thread's 32 clusters stay in
+// registers; the bucket counts (kPieceBuckets) sit in LDS.  The buckets are
+// taken in pieces of consecutive buckets holding at most kPieceCap clusters,
+// whose keys are placed in LDS in their buckets: every access of the rank
+// computation is an LDS access.  A piece's ranks are consecutive, so its order
+// and rank-prefix entries leave in order.  A head's buckets are shared by
+// the workgroups of its grid column (blockIdx.y): each counts every cluster
+// (the bucket starts must be known everywhere), then ranks only the pieces of
+// its own run of whole buckets, its prefix starting at the tokens of the
+// clusters before them, and finds the sampled rows that fall in its ranks, in
+// LDS when its share is one piece.  The workgroups exchange nothing; the first
+// one also writes the head record.  Only the clusters of the own share take
+// an LDS place (a returning counter update for each of a head's clusters, a
+// position kept for each and the ranks handed back through it had made it 62.8
+// us at 32768 clusters x 32 heads, eight workgroups each; now %P% us).
 constexpr int kPieceBuckets = 4096;
 constexpr int kPiecePer = 6;                    // entries per thread in the piece scan
 constexpr int kPieceCap = kPiecePer * 1024;     // clusters per piece
 constexpr int kPieceMaxC = 32 * 1024;           // 32 clusters per thread
 constexpr size_t kPieceLdsBytes = (size_t)kPieceBuckets * 8 + (size_t)kPieceCap * 20;
+constexpr int kPieceOrdAt = kPieceBuckets * 8 + kPieceCap * 12;  // LDS offsets: ids by rank in the piece,
+constexpr int kPieceSizeAt = kPieceOrdAt + kPieceCap * 4;        // sizes, then prefix, by rank
 // dynamic LDS of the workspace sort: the pieces, or 8192 bucket counts and
 // starts on the general path; then the rank prefix for the sample search
 constexpr size_t kSortWsLdsBytes = kPieceLdsBytes > (size_t)kSortLdsBuckets * 8 ? kPieceLdsBytes : (size_t)kSortLdsBuckets * 8;
@@ -300,6 +308,7 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
   __shared__ uint32_t s_wave_u[17];
   __shared__ float s_wave_f[17];
   __shared__ __align__(16) float s_red[16][4];
+  __shared__ int s_any_n;  // workspace sort: clusters of the piece collected so far
   const int tid = threadIdx.x, nt = blockDim.x;
   const int bh = blockIdx.x;
   const int b = bh / a.Hq, h = bh % a.Hq, g = h / a.G;
@@ -340,6 +349,7 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
   // (tok_lo, tok_hi]; the whole order except when a head's pieces are shared
   int rk_lo = 0, rk_hi = -1;
   uint32_t tok_lo = 0, tok_hi = 0;
+  bool one_piece = false;  // that share in one piece: prefix and ids in LDS
   if constexpr (kLds) {
     // LDS: keys u64[nb] (after ranking: ostart i32[nb] by cluster, ord_s i32[nb]
     // by rank), cnt u32[nb], start u32[nb].  Compact: keys u32[nb], ids u16[nb],
@@ -579,30 +589,52 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
       uint32_t* s_aux = reinterpret_cast<uint32_t*>(s_keys + kPieceCap);  // size by position, then rank
       int32_t* s_ord = reinterpret_cast<int32_t*>(s_aux + kPieceCap);     // cluster by rank in the piece
       uint32_t* s_sz = reinterpret_cast<uint32_t*>(s_ord + kPieceCap);    // size, then prefix, by rank
-      float v[kP];     // the score, then the rank
-      uint32_t ps[kP];  // size (low 16 bits) | place in its bucket, then bucket position (high 16 bits)
+      float v[kP];      // the score
+      uint32_t ps[kP];  // size (low 16 bits, 0 past C) | bucket (high 16 bits, 0xffff past C)
       uint32_t size_or = 0;  // OR of the sizes: any bit above 15 sends the head to the general path
-      const int nv = C > tid ? (C - tid + 1023) / 1024 : 0;  // clusters of this thread: tid + 1024 e, e < nv
-      // the cluster id, rebuilt at each use rather than kept in 32 registers
+      // this thread's clusters: four consecutive ones per 4096, cid(e), e < kP,
+      // below C (rebuilt at each use rather than kept in registers)
       auto cid = [&](int e) {
-        int t = tid;
+        int t = tid * 4;
         asm volatile("" : "+v"(t));
-        return t + e * 1024;
+        return t + (e >> 2) * 4096 + (e & 3);
       };
+      const int room = C - 4 * tid;
+      auto valid = [&](int e) { return (e >> 2) * 4096 + (e & 3) < room; };
+      // scores, then the offsets in two batches, 16 bytes per load (cluster by
+      // cluster they had taken 12.4 us of the kernel); a group that straddles
+      // C takes single loads at clamped indices
+      typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
+      typedef int i32x4a __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
-      for (int e = 0; e < kP; ++e) v[e] = sc[min(cid(e), C - 1)];
+      for (int e = 0; e < kP; e += 4) {
+        const int j = cid(e);
+        if (j + 4 <= C) {
+          const f32x4a x = *reinterpret_cast<const f32x4a*>(sc + j);
+          v[e] = x.x, v[e + 1] = x.y, v[e + 2] = x.z, v[e + 3] = x.w;
+        } else {
 #pragma unroll
-      for (int e0 = 0; e0 < kP; e0 += kP / 2) {  // sizes: 32 offset loads in flight per batch
-        int o0[kP / 2], o1[kP / 2];
+          for (int i = 0; i < 4; ++i) v[e + i] = sc[min(j + i, C - 1)];
+        }
+      }
 #pragma unroll
-        for (int e = 0; e < kP / 2; ++e) {
-          const int jc = min(cid(e0 + e), C - 1);
-          o0[e] = off[jc];
-          o1[e] = off[jc + 1];
+      for (int e0 = 0; e0 < kP; e0 += kP / 2) {
+        int o[kP / 2], last[kP / 8];  // first rows; the row after each group
+#pragma unroll
+        for (int e = 0; e < kP / 2; e += 4) {
+          const int j = cid(e0 + e);
+          if (j + 4 <= C) {
+            const i32x4a x = *reinterpret_cast<const i32x4a*>(off + j);
+            o[e] = x.x, o[e + 1] = x.y, o[e + 2] = x.z, o[e + 3] = x.w;
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[e + i] = off[min(j + i, C)];
+          }
+          last[e / 4] = off[min(j + 4, C)];
         }
 #pragma unroll
         for (int e = 0; e < kP / 2; ++e) {
-          uint32_t x = (uint32_t)(o1[e] - o0[e]);
+          uint32_t x = (uint32_t)((e % 4 == 3 ? last[e / 4] : o[e + 1 < kP / 2 ? e + 1 : e]) - o[e]);  // (0 from C on)
           size_or |= x;
           // taken now, so that the loaded offsets die here
           asm volatile("" : "+v"(x), "+v"(size_or));
@@ -610,12 +642,13 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
         }
       }
       reinterpret_cast<uint4*>(cnt_l)[tid] = make_uint4(0, 0, 0, 0);
+      if (tid == 0) s_any_n = 0;
       float sm = 0.f, sq = 0.f, mu, inv_sd;
       int nf = 0;  // of the wave
       bool diff = false, all_equal;  // (all equal: the general path orders them by id)
 #pragma unroll
       for (int e = 0; e < kP; ++e) {
-        const bool num = e < nv && v[e] == v[e];
+        const bool num = valid(e) && v[e] == v[e];
         const float d = num ? v[e] - pivot : 0.f;
         sm += d;
         sq = fmaf(d, d, sq);
@@ -625,14 +658,14 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
       // (its barrier also orders the count clears before the counting below)
       score_moments(pivot, sm, sq, nf, diff, C, s_red, &mu, &inv_sd, &all_equal);
       if (!all_equal) {
-        // counting: each cluster's place in its bucket (arrival order)
+        // counting (adding 0 past C, so that no branch parts the 32 updates);
+        // each cluster keeps its bucket
 #pragma unroll
-        for (int e0 = 0; e0 < kP; e0 += 8) {  // unconditional (adding 0 past C): 8 returns in flight
-#pragma unroll
-          for (int e = e0; e < e0 + 8; ++e)
-            ps[e] |= atomicAdd(&cnt_l[score_bucket(v[e], mu, inv_sd, nbk)], e < nv ? 1u : 0u) << 16;
-#pragma unroll
-          for (int e = e0; e < e0 + 8; ++e) asm volatile("" : "+v"(ps[e]));  // done before the next 8
+        for (int e = 0; e < kP; ++e) {
+          const uint32_t bk = (uint32_t)score_bucket(v[e], mu, inv_sd, nbk);
+          atomicAdd(&cnt_l[bk], valid(e) ? 1u : 0u);
+          ps[e] |= (valid(e) ? bk : 0xffffu) << 16;
+          asm volatile("" : "+v"(ps[e]));  // done before the next: the registers are full
         }
         __syncthreads();
         // the largest bucket must fit a piece
@@ -642,17 +675,10 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
         mb = wave_allmax_f(size_or > 0xffffu ? INFINITY : mb);
         if ((tid & (kWave - 1)) == 0) s_wave_f[tid / kWave] = mb;
         scan_lds<nbk / 1024>(st_l, s_wave_u);  // bucket starts; its barriers publish s_wave_f
-        float maxb = 0.f;
-        for (int w = 0; w < 1024 / kWave; ++w) maxb = fmaxf(maxb, s_wave_f[w]);
+        const float maxb = wave_allmax_f(s_wave_f[tid & 15]);
         pieces_done = maxb <= (float)kPieceCap;
-        // bucket position = bucket start + place (C <= 2^15: 16 bits)
-#pragma unroll
-        for (int e0 = 0; e0 < kP; e0 += 8) {  // 8 reads in flight
-#pragma unroll
-          for (int e = e0; e < e0 + 8; ++e) ps[e] += st_l[score_bucket(v[e], mu, inv_sd, nbk)] << 16;
-#pragma unroll
-          for (int e = e0; e < e0 + 8; ++e) asm volatile("" : "+v"(ps[e]));
-        }
+        // the counts become the buckets' placing cursors
+        reinterpret_cast<uint4*>(cnt_l)[tid] = reinterpret_cast<const uint4*>(st_l)[tid];
       }
       if (pieces_done) {
         int32_t* rpre = a.rprefix + (int64_t)bh * (a.Cm + 1);
@@ -679,28 +705,20 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
           }
         }
         __syncthreads();
-        b_lo = 0;
-        b_hi = 0;
-        for (int w = 0; w < 1024 / kWave; ++w) {
-          b_lo += (int)s_wave_u[w];
-          b_hi += (int)s_cnt2[w];
-        }
+        b_lo = (int)sum_of_waves(s_wave_u);
+        b_hi = (int)sum_of_waves(s_cnt2);
         if (kw == 0) b_lo = 0;        // (the buckets before are empty)
         if (kw == nw - 1) b_hi = nbk;  // (every bucket start is at most C)
-        // uniform over the workgroup: kept in scalar registers (the thread's
-        // 32 scores and sizes fill its vector registers)
-        b_lo = __builtin_amdgcn_readfirstlane(b_lo);
-        b_hi = __builtin_amdgcn_readfirstlane(b_hi);
         const uint32_t r_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b_lo < nbk ? st_l[b_lo] : (uint32_t)C));
         const uint32_t r_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b_hi < nbk ? st_l[b_hi] : (uint32_t)C));
         {
-          // tokens of the clusters ranked before r_lo, and of all clusters
+          // tokens of the clusters in the buckets before b_lo, and of all clusters
           uint32_t before = 0, all = 0;
 #pragma unroll
           for (int e = 0; e < kP; ++e) {
-            const uint32_t sz = e < nv ? (ps[e] & 0xffffu) : 0u;
+            const uint32_t sz = ps[e] & 0xffffu;
             all += sz;
-            before += (ps[e] >> 16) < r_lo ? sz : 0u;
+            before += (ps[e] >> 16) < (uint32_t)b_lo ? sz : 0u;
           }
           before = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(before), kWave - 1);
           all = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(all), kWave - 1);
@@ -710,14 +728,8 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
           }
         }
         __syncthreads();  // (s_wave_u was read before it: the piece loop may write it)
-        uint32_t carry = 0;
-        total = 0;
-        for (int w = 0; w < 1024 / kWave; ++w) {
-          carry += s_cnt2[16 + w];
-          total += s_cnt2[32 + w];
-        }
-        carry = (uint32_t)__builtin_amdgcn_readfirstlane((int)carry);
-        total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
+        uint32_t carry = sum_of_waves(s_cnt2 + 16);
+        total = sum_of_waves(s_cnt2 + 32);
         rk_lo = (int)r_lo;
         rk_hi = (int)r_hi;
         tok_lo = carry;
@@ -736,27 +748,49 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
             if ((tid & (kWave - 1)) == 0) s_wave_u[tid / kWave] = c;
           }
           __syncthreads();  // also: the previous piece's LDS reads are done
-          int b1 = 0;
-          for (int w = 0; w < 1024 / kWave; ++w) b1 += (int)s_wave_u[w];
-          b1 = min(b1, b_hi);
+          const int b1 = min((int)sum_of_waves(s_wave_u), b_hi);
           const uint32_t len = (b1 < nbk ? st_l[b1] : (uint32_t)C) - p0;
+          // the piece's clusters, in no order, as key | id | size to LDS (in the
+          // space of the results by rank), a wave reserving room for all of its
+          // own, then, four to six per thread, to their buckets (a counter
+          // update per register, each waited for, had taken 14.8 us)
+          uint64_t* s_any = reinterpret_cast<uint64_t*>(s_ord);
+          static_assert(kPieceSizeAt == kPieceOrdAt + kPieceCap * 4, "two arrays of 4 bytes make one of 8");
+          auto inside = [&](int e) { return (ps[e] >> 16) - (uint32_t)b0 < (uint32_t)(b1 - b0); };
+          uint32_t mine = 0;
 #pragma unroll
-          for (int e = 0; e < kPiecePer; ++e) s_sz[tid * kPiecePer + e] = 0u;
-          // the owners place the piece's keys and sizes at their bucket positions
+          for (int e = 0; e < kP; ++e) mine += inside(e) ? 1u : 0u;
+          const uint32_t incl = wave_incl_scan(mine);
+          int pos = 0;
+          if ((tid & (kWave - 1)) == kWave - 1 && incl) pos = atomicAdd(&s_any_n, (int)incl);
+          pos = __builtin_amdgcn_readlane(pos, kWave - 1) + (int)(incl - mine);
 #pragma unroll
           for (int e = 0; e < kP; ++e) {
-            const uint32_t pos = (ps[e] >> 16) - p0;
-            if (e < nv && pos < len) {
-              s_keys[pos] = ((uint64_t)desc_key_bits(v[e]) << 32) | (uint32_t)cid(e);
-              s_aux[pos] = ps[e] & 0xffffu;
+            if (inside(e)) {
+              s_any[min(pos, kPieceCap - 1)] = ((uint64_t)desc_key_bits(v[e]) << 32) | (uint64_t)((uint32_t)cid(e) << 16) | (ps[e] & 0xffffu);
+              ++pos;
             }
           }
           __syncthreads();
+          if (tid == 0) s_any_n = 0;
+#pragma unroll
+          for (int k = 0; k < kPiecePer; ++k) {
+            const int t = tid + k * 1024;
+            if (t < (int)len) {
+              const uint64_t x = s_any[t];
+              const int bk = score_bucket(key_score((uint32_t)(x >> 32)), mu, inv_sd, nbk);
+              const uint32_t pos = min(atomicAdd(&cnt_l[bk], 1u) - p0, (uint32_t)kPieceCap - 1);
+              s_keys[pos] = (x >> 32 << 32) | ((uint32_t)x >> 16);
+              s_aux[pos] = (uint32_t)x & 0xffffu;
+            }
+          }
+          __syncthreads();
+          for (int t = (int)len + tid; t < kPieceCap; t += 1024) s_sz[t] = 0u;
           // by position: rank = bucket start + smaller keys of the bucket
           for (int t = tid; t < (int)len; t += 1024) {
             const uint64_t key = s_keys[t];
             const int bk = score_bucket(key_score((uint32_t)(key >> 32)), mu, inv_sd, nbk);
-            const uint32_t beg = st_l[bk] - p0, end = beg + cnt_l[bk];
+            const uint32_t beg = st_l[bk] - p0, end = cnt_l[bk] - p0;  // (the cursor ended there)
             uint32_t r = beg, i = beg;
             for (; i + 4 <= end; i += 4) {  // four reads in flight
               const uint64_t k0 = s_keys[i], k1 = s_keys[i + 1], k2 = s_keys[i + 2], k3 = s_keys[i + 3];
@@ -765,34 +799,21 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
             for (; i < end; ++i) r += s_keys[i] < key ? 1u : 0u;
             s_ord[r] = (int32_t)(uint32_t)key;
             s_sz[r] = s_aux[t];
-            s_aux[t] = p0 + r;
+            rank_of[(uint32_t)key] = (int32_t)(p0 + r);
           }
           __syncthreads();
-#pragma unroll
-          for (int e0 = 0; e0 < kP; e0 += 8) {  // reads at clamped positions, 8 in flight
-#pragma unroll
-            for (int e = e0; e < e0 + 8; ++e) {
-              const uint32_t pos = (ps[e] >> 16) - p0;
-              const uint32_t rk = s_aux[min(pos, (uint32_t)kPieceCap - 1)];
-              v[e] = (e < nv && pos < len) ? __uint_as_float(rk) : v[e];
-            }
-#pragma unroll
-            for (int e = e0; e < e0 + 8; ++e) asm volatile("" : "+v"(v[e]));
-          }
           const uint32_t tot = scan_lds<kPiecePer>(s_sz, s_wave_u);
+          // (one piece for the whole share: its prefix and ids stay in LDS for
+          // the sample search)
+          one_piece = b0 == b_lo && b1 == b_hi;
           for (int t = tid; t < (int)len; t += 1024) {
             const uint32_t pf = carry + s_sz[t];
             order[p0 + t] = s_ord[t];
-            cnt[p0 + t] = pf;
+            if (!one_piece) cnt[p0 + t] = pf;
             rpre[p0 + t] = (int32_t)pf;
           }
           carry += tot;
           b0 = b1;
-        }
-#pragma unroll
-        for (int e = 0; e < kP; ++e) {
-          const uint32_t pos = ps[e] >> 16;
-          if (e < nv && pos >= r_lo && pos < r_hi) rank_of[cid(e)] = (int32_t)__float_as_uint(v[e]);
         }
         if (tid == 0 && kw == 0) rpre[C] = (int32_t)total;
         tok_hi = carry;
@@ -1021,6 +1042,48 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
     const int r0 = whole ? 0 : rk_lo, R = whole ? C : rk_hi - rk_lo;
     const int64_t p_lo = whole ? 0 : tok_lo, p_hi = whole ? (int64_t)total : tok_hi;
     if (R <= 0) return;
+    // positions and prefixes in 32 bits (a sequence holds fewer than 2^31
+    // tokens).  The sampled positions are runs of three regions (exact head 1..N,
+    // the two windows): region rg has the samples [u_beg, u_end) at positions
+    // pos0, pos0 + 1, ...
+    const int N32 = (int)N, NW = (int)(N + W1), s1 = (int)geo.s1, s2 = (int)geo.s2, Sm = (int)S_main;
+    auto region = [&](int rg, int* u_beg, int* u_end, int* pos0) {
+      *u_beg = rg == 0 ? 0 : (rg == 1 ? min(N32, Sm) : min(NW, Sm));
+      *u_end = rg == 0 ? min(N32, Sm) : (rg == 1 ? min(NW, Sm) : Sm);
+      *pos0 = rg == 0 ? 1 : (rg == 1 ? s1 : s2);
+    };
+    if (one_piece) {
+      // the ranks' prefix (less p_lo) and ids are in LDS: each rank that a region
+      // touches has its rows written by its wave (the exact head lies in the
+      // first workgroup's ranks alone: a search per sample there, 10486 of
+      // them in 1048576 tokens, had taken 14.6 us)
+      const int32_t* s_ids = reinterpret_cast<const int32_t*>(smem_raw + kPieceOrdAt);
+      const uint32_t* s_pre = reinterpret_cast<const uint32_t*>(smem_raw + kPieceSizeAt);
+      const int lane = tid & (kWave - 1);
+      for (int t0 = 0; t0 < R; t0 += nt) {
+        const int t = t0 + tid, tc = min(t, R - 1);
+        // the rank's positions p + 1 .. q
+        const int p = (int)(s_pre[tc] + (uint32_t)p_lo), q = t + 1 < R ? (int)(s_pre[tc + 1] + (uint32_t)p_lo) : (int)p_hi;
+        for (int rg = 0; rg < 3; ++rg) {
+          int u_beg, u_end, pos0;
+          region(rg, &u_beg, &u_end, &pos0);
+          const int last = pos0 + (u_end - u_beg) - 1;
+          const bool act = t < R && p < last && q >= pos0;  // (an empty region: last < pos0 <= q, p < q)
+          uint64_t mask = __ballot(act);
+          if (!mask) continue;
+          const int first = off[act ? s_ids[tc] : 0];
+          for (; mask; mask &= mask - 1) {
+            const int l = __ffsll((long long)mask) - 1;
+            const int P = __builtin_amdgcn_readlane(p, l), Q = __builtin_amdgcn_readlane(q, l);
+            const int F = __builtin_amdgcn_readlane(first, l);
+            const int lo = max(P + 1, pos0), hi = min(Q, last);
+            for (int64_t i = lo + lane; i <= hi; i += kWave)
+              rows[u_beg + (i - pos0)] = min(max(F + (int32_t)(i - 1 - P), 0), n - 1);
+          }
+        }
+      }
+      return;
+    }
     uint32_t* s_pre = reinterpret_cast<uint32_t*>(smem_raw);
     constexpr int kPreCap = (int)(kSortWsLdsBytes / 4);
     const int kStr = (R + kPreCap - 1) / kPreCap;
@@ -1037,14 +1100,9 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
     int top = 1;
     while (top * 2 <= nsp) top <<= 1;
     constexpr int kU = 8;  // independent searches in flight per thread
-    // positions and prefixes in 32 bits (a sequence holds fewer than 2^31
-    // tokens).  The sampled positions of each region (exact head 1..N, the
-    // two windows) that fall in (p_lo, p_hi] are a run of sample indices.
-    const int N32 = (int)N, NW = (int)(N + W1), s1 = (int)geo.s1, s2 = (int)geo.s2, Sm = (int)S_main;
     for (int rg = 0; rg < 3; ++rg) {
-      const int u_beg = rg == 0 ? 0 : (rg == 1 ? min(N32, Sm) : min(NW, Sm));
-      const int u_end = rg == 0 ? min(N32, Sm) : (rg == 1 ? min(NW, Sm) : Sm);
-      const int64_t pos0 = rg == 0 ? 1 : (rg == 1 ? s1 : s2);  // position of sample u_beg
+      int u_beg, u_end, pos0;
+      region(rg, &u_beg, &u_end, &pos0);
       // the samples u in [u_beg, u_end) whose position pos0 + (u - u_beg) is in (p_lo, p_hi]
       const int ua = (int)max((int64_t)u_beg, u_beg + (p_lo + 1 - pos0));
       const int ub = (int)min((int64_t)u_end, u_beg + (p_hi + 1 - pos0));
@@ -1087,10 +1145,9 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
         int first[kU];
         uint32_t pr[kU];
 #pragma unroll
-        for (int k = 0; k < kU; ++k) {
-          lr[k] = min(lr[k], R - 1);
-          first[k] = off[order[r0 + lr[k]]];
-        }
+        for (int k = 0; k < kU; ++k) lr[k] = min(lr[k], R - 1);
+#pragma unroll
+        for (int k = 0; k < kU; ++k) first[k] = off[order[r0 + lr[k]]];
         // the rank's prefix from LDS when every entry is there (kept apart from
         // the memory read so that each compiles to its own instruction kind)
         if (kStr == 1) {
