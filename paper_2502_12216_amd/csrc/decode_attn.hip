@@ -131,20 +131,96 @@ __device__ __forceinline__ float head_value(float x, int h) {
   }
 }
 
+// Value of lane h of the row (h < 8, a constant after unrolling), by DPP row_newbcast
+__device__ __forceinline__ float row_lane(float x, int h) {
+  switch (h) {
+    case 0: return dpp<0x150>(x);
+    case 1: return dpp<0x151>(x);
+    case 2: return dpp<0x152>(x);
+    case 3: return dpp<0x153>(x);
+    case 4: return dpp<0x154>(x);
+    case 5: return dpp<0x155>(x);
+    case 6: return dpp<0x156>(x);
+    default: return dpp<0x157>(x);
+  }
+}
+
+// The same sums of 8 heads, bitwise (the same tree: lane i with 15 - i, with 7 - i,
+// quad swaps), for the matrix form, ending in head sl mod 8: the halving steps
+// are those over the lane bits 2, 1 and 0.
+__device__ __forceinline__ float reduce_heads_mod8(const float (&v)[8], int sl) {
+  float b[8], a[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) b[i] = v[i] + dpp<0x140>(v[i]);  // row_mirror
+  const bool up2 = sl & 4;  // row_half_mirror
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float keep = up2 ? b[4 + i] : b[i], send = up2 ? b[i] : b[4 + i];
+    a[i] = keep + dpp<0x141>(send);
+  }
+  const bool up1 = sl & 2;  // quad_perm [2,3,0,1]
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const float keep = up1 ? a[2 + i] : a[i], send = up1 ? a[i] : a[2 + i];
+    c[i] = keep + dpp<0x4E>(send);
+  }
+  const bool up0 = sl & 1;  // quad_perm [1,0,3,2]
+  const float keep = up0 ? c[1] : c[0], send = up0 ? c[0] : c[1];
+  return keep + dpp<0xB1>(send);
+}
+
+typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// Two 16-bit halves of two words, low halves or high halves, as one word
+__device__ __forceinline__ uint32_t pack_lo(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+__device__ __forceinline__ short4_t pair4(uint32_t lo, uint32_t hi) {
+  u32x2 w;
+  w.x = lo;
+  w.y = hi;
+  return __builtin_bit_cast(short4_t, w);
+}
+
+// Four fp32 weights in [0, 1] as three bf16 operands whose sum is exact: the upper
+// 8 bits of the significand, the next 8 of the rest, the rest.  The second and
+// third of a weight that is not zero are at least 2^-126 (2^-126 of the
+// largest weight, below any rounding), so that its product with an infinite
+// value is that infinity, as in one multiplication, and not 0 x inf.
+__device__ __forceinline__ void split_weights(const float (&p)[4], short4_t (&part)[3]) {
+  uint32_t h[4], m[4], r[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float least = fminf(p[i], 0x1p-126f);
+    h[i] = __float_as_uint(p[i]);
+    const float x = p[i] - __uint_as_float(h[i] & 0xffff0000u);
+    m[i] = __float_as_uint(fmaxf(x, least));
+    r[i] = __float_as_uint(fmaxf(x - __uint_as_float(__float_as_uint(x) & 0xffff0000u), least));
+  }
+  part[0] = pair4(pack_hi(h[0], h[1]), pack_hi(h[2], h[3]));
+  part[1] = pair4(pack_hi(m[0], m[1]), pack_hi(m[2], m[3]));
+  part[2] = pair4(pack_hi(r[0], r[1]), pack_hi(r[2], r[3]));
+}
+
 // 16 lanes share one 256-byte row (16 B per lane); a lane-group streams TOK
 // rows per tile.
-#ifndef TACTIC_ATTN_TOK
-#define TACTIC_ATTN_TOK 2
-#endif
-#ifndef TACTIC_ATTN_DEPTH
-#define TACTIC_ATTN_DEPTH 2  // tiles in flight while one is consumed
-#endif
-#ifndef TACTIC_ATTN_WPE
-#define TACTIC_ATTN_WPE 3  // resident waves per SIMD the register budget must allow
-#endif
+constexpr int attn_tok(int G) { return G == 8 ? 4 : 2; }
 
+// G < 8: TOK = 2, p * v on the vector unit.  G = 8 (matrix form): TOK = 4, and the
+// four tokens x four heads of a lane's dimension are one
+// v_mfma_f32_4x4x4_16b_bf16 per bf16 part of p (three parts, an exact split of
+// the fp32 weight; V is bf16, products exact, fp32 accumulators): block lane / 4
+// has the lane's dimension as its column lane % 4 and the weights of a head as its
+// row lane % 4, so operands and results stay in the lane that loaded the row,
+// and 256 multiply-adds, 32 unpacks and 32 broadcasts per lane and four tokens
+// become 48 matrix instructions, 16 packs, 68 to split the weights and 12 to
+// exchange them.  The vector unit had been busy about 70% of the time at two
+// waves per SIMD: 97126 tokens, 8 KV heads, a quarter selected: 49.1 -> 43.3 us, the
+// error against 64 bits unchanged (2.7e-7 to 6.8e-7 over seeds).  For G = 4
+// (64% busy at three waves) the same form gains 2% on a large selection and
+// loses 1% on small ones and paged dense decode.
 template <int G, int TOK, bool kPaged>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G >= 8 ? 2 : TACTIC_ATTN_WPE)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G >= 8 ? 2 : 3)))
 void attn_splitk_kernel(AttnArgs a) {
   constexpr int LPR = 16;                 // lanes per 256-byte row
   constexpr int kPart = G * (kHeadDim + 2);
@@ -153,6 +229,8 @@ void attn_splitk_kernel(AttnArgs a) {
   constexpr int GPW = kWave / LPR;        // lane-groups per wave
   constexpr int NG = 4 * GPW;             // lane-groups per workgroup
   constexpr int kTileTok = NG * TOK;      // tokens per workgroup tile
+  constexpr bool kMatrix = G == 8;
+  static_assert(TOK == attn_tok(G), "the matrix form takes four tokens per lane-group");
   extern __shared__ int64_t s_prefix[];  // [B * NV + 1] split units before each selection group
   // the row table of a sub-range is dead once the merge starts, so the
   // merge's partial sums reuse its storage
@@ -239,12 +317,19 @@ void attn_splitk_kernel(AttnArgs a) {
 
     // online-softmax state: the running max and sum of this lane's head hl
     // (identical in the 16 / G lanes of that head), the accumulators of every head
-    const int hl = sl / (16 / G);
-    float m = -INFINITY, l = 0.f, acc[G][EPL];
+    const int hl = kMatrix ? sl % G : sl / (16 / G);
+    float m = -INFINITY, l = 0.f;
+    // accumulators of head h, dimension e: element h % 4 of accv[h / 4][e]
+    constexpr int kHV = (G + 3) / 4;
+    f32x4_t accv[kHV][EPL];
 #pragma unroll
-    for (int h = 0; h < G; ++h)
+    for (int q = 0; q < kHV; ++q)
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[h][e] = 0.f;
+      for (int e = 0; e < EPL; ++e) accv[q][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto of_head = [&](float x, int h) {  // the value of head h from a lane that holds it
+      if constexpr (kMatrix) return row_lane(x, h);
+      else return head_value<G>(x, h);
+    };
 
     // contiguous: rows of this (sequence, KV head); paged: row indices into the page array
     const int64_t rbase = kPaged ? 0 : (int64_t)kvh * a.total + kvb;
@@ -255,21 +340,36 @@ void attn_splitk_kernel(AttnArgs a) {
     int cnt = 0;      // tokens of the current sub-range
     int64_t p0 = 0;   // its first position in the group's token list
     struct Tile {
-      uint32_t k[TOK][W];
-      uint32_t v[TOK][W];
+      uint4 k[TOK], v[TOK];
     };
-    auto load_tile = [&](int tile) -> Tile {
+    auto word = [](const uint4& x, int w) __attribute__((always_inline)) {
+      return w == 0 ? x.x : (w == 1 ? x.y : (w == 2 ? x.z : x.w));
+    };
+    // the lane-group's rows of a tile; positions past the sub-range load
+    // nothing and hold zeros (a tile inside it has no branch per row)
+    auto load_tile = [&](int tile) __attribute__((always_inline)) -> Tile {
       Tile r;
+      const int tb = tile * kTileTok + gid * TOK;
+      if (kMatrix && (tile + 1) * kTileTok <= cnt) {
+        int64_t row[TOK];
 #pragma unroll
-      for (int i = 0; i < TOK; ++i) {
-        const int t = tile * kTileTok + gid * TOK + i;
-        if (t < cnt) {
-          const int64_t row = (a.dense && !kPaged) ? p0 + t : (int64_t)s_rows[t];
-          load_words(Kb + row * kHeadDim, r.k[i]);
-          load_words(Vb + row * kHeadDim, r.v[i]);
-        } else {
+        for (int i = 0; i < TOK; ++i) row[i] = (a.dense && !kPaged) ? p0 + tb + i : (int64_t)s_rows[tb + i];
 #pragma unroll
-          for (int w = 0; w < W; ++w) r.k[i][w] = r.v[i][w] = 0u;
+        for (int i = 0; i < TOK; ++i) {
+          r.k[i] = load_stream16(Kb + row[i] * kHeadDim);
+          r.v[i] = load_stream16(Vb + row[i] * kHeadDim);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < TOK; ++i) {
+          const int t = tb + i;
+          if (t < cnt) {
+            const int64_t row = (a.dense && !kPaged) ? p0 + t : (int64_t)s_rows[t];
+            r.k[i] = load_stream16(Kb + row * kHeadDim);
+            r.v[i] = load_stream16(Vb + row * kHeadDim);
+          } else {
+            r.k[i] = r.v[i] = make_uint4(0u, 0u, 0u, 0u);
+          }
         }
       }
       return r;
@@ -277,7 +377,7 @@ void attn_splitk_kernel(AttnArgs a) {
     // one tile of TOK tokens per lane-group: logits of the G heads (each lane
     // ends with its own head's), running max (rescale only when some group's
     // max grows), p * v with each head's weight broadcast from its lanes
-    auto consume = [&](const Tile& x, int tile) {
+    auto consume = [&](const Tile& x, int tile) __attribute__((always_inline)) {
       float s[TOK];
 #pragma unroll
       for (int i = 0; i < TOK; ++i) {
@@ -287,9 +387,11 @@ void attn_splitk_kernel(AttnArgs a) {
         for (int h = 0; h < G; ++h) {
           d[h] = 0.f;
 #pragma unroll
-          for (int w = 0; w < W; ++w) d[h] = dot2_bf16(x.k[i][w], qw[h][w], d[h]);
+          for (int w = 0; w < W; ++w) d[h] = dot2_bf16(word(x.k[i], w), qw[h][w], d[h]);
         }
-        const float r = reduce_heads<G>(d, sl);
+        float r;
+        if constexpr (kMatrix) r = reduce_heads_mod8(d, sl);
+        else r = reduce_heads<G>(d, sl);
         s[i] = valid ? r * kScaleLog2 : -INFINITY;
       }
       float mn = m;
@@ -300,11 +402,50 @@ void attn_splitk_kernel(AttnArgs a) {
         m = mn;
         l *= corr;
 #pragma unroll
-        for (int h = 0; h < G; ++h) {
-          const float c = head_value<G>(corr, h);
+        for (int q = 0; q < kHV; ++q) {
+          f32x4_t c;
+          c.x = of_head(corr, 4 * q);
+          c.y = G > 1 ? of_head(corr, 4 * q + 1) : 1.f;
+          c.z = G > 2 ? of_head(corr, 4 * q + 2) : 1.f;
+          c.w = G > 2 ? of_head(corr, 4 * q + 3) : 1.f;
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) acc[h][e] *= c;
+          for (int e = 0; e < EPL; ++e) accv[q][e] *= c;
         }
+      }
+      if constexpr (kMatrix) {
+        float p[4];
+#pragma unroll
+        for (int i = 0; i < TOK; ++i) {
+          p[i] = s[i] == -INFINITY ? 0.f : fast_exp2(s[i] - m);
+          l += p[i];
+        }
+        // heads lane % 4 and lane % 4 + 4: this lane's and the one four lanes on
+        short4_t part[2][3];
+        float lo[4], hi[4];
+        const bool up = sl & 4;
+#pragma unroll
+        for (int i = 0; i < TOK; ++i) {
+          const float o = dpp<0x12C>(p[i]);  // row_ror:12
+          lo[i] = up ? o : p[i];
+          hi[i] = up ? p[i] : o;
+        }
+        split_weights(lo, part[0]);
+        split_weights(hi, part[1]);
+        short4_t vt[EPL];  // the four tokens' values of each dimension
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          const uint32_t v0 = word(x.v[0], w), v1 = word(x.v[1], w), v2 = word(x.v[2], w), v3 = word(x.v[3], w);
+          vt[2 * w] = pair4(pack_lo(v0, v1), pack_lo(v2, v3));
+          vt[2 * w + 1] = pair4(pack_hi(v0, v1), pack_hi(v2, v3));
+        }
+#pragma unroll
+        for (int q = 0; q < kHV; ++q)
+#pragma unroll
+          for (int k = 2; k >= 0; --k)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e)
+              accv[q][e] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(part[q][k], vt[e], accv[q][e], 0, 0, 0);
+        return;
       }
 #pragma unroll
       for (int i = 0; i < TOK; ++i) {
@@ -313,14 +454,14 @@ void attn_splitk_kernel(AttnArgs a) {
         float vf[EPL];
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-          vf[2 * w] = bf16lo(x.v[i][w]);
-          vf[2 * w + 1] = bf16hi(x.v[i][w]);
+          vf[2 * w] = bf16lo(word(x.v[i], w));
+          vf[2 * w + 1] = bf16hi(word(x.v[i], w));
         }
 #pragma unroll
         for (int h = 0; h < G; ++h) {
-          const float ph = head_value<G>(p, h);
+          const float ph = of_head(p, h);
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) acc[h][e] = fmaf(ph, vf[e], acc[h][e]);
+          for (int e = 0; e < EPL; ++e) accv[h / 4][e][h % 4] = fmaf(ph, vf[e], accv[h / 4][e][h % 4]);
         }
       }
     };
@@ -420,50 +561,37 @@ void attn_splitk_kernel(AttnArgs a) {
         __syncthreads();
       }
       const int ntile = (cnt + kTileTok - 1) / kTileTok;
-#if TACTIC_ATTN_DEPTH == 2
-      // two tiles in flight while one is consumed (rotation unrolled by three)
-      Tile t0 = load_tile(0), t1 = load_tile(1);
+      if constexpr (kMatrix) {
+        // one tile of four tokens in flight while one is consumed
+        Tile t0 = load_tile(0);
 #pragma unroll 1
-      for (int tile = 0; tile < ntile; tile += 3) {
-        Tile t2 = load_tile(tile + 2);
-        consume(t0, tile);
-        if (tile + 1 >= ntile) break;
-        t0 = load_tile(tile + 3);
-        consume(t1, tile + 1);
-        if (tile + 2 >= ntile) break;
-        t1 = load_tile(tile + 4);
-        consume(t2, tile + 2);
-      }
-#elif TACTIC_ATTN_DEPTH == 3
-      Tile t0 = load_tile(0), t1 = load_tile(1), t2 = load_tile(2);
+        for (int tile = 0; tile < ntile; tile += 2) {
+          const Tile t1 = load_tile(tile + 1);
+          consume(t0, tile);
+          if (tile + 1 >= ntile) break;
+          t0 = load_tile(tile + 2);
+          consume(t1, tile + 1);
+        }
+      } else {
+        // two tiles of two tokens in flight while one is consumed (rotation unrolled by three)
+        Tile t0 = load_tile(0), t1 = load_tile(1);
 #pragma unroll 1
-      for (int tile = 0; tile < ntile; tile += 4) {
-        Tile t3 = load_tile(tile + 3);
-        consume(t0, tile);
-        if (tile + 1 >= ntile) break;
-        t0 = load_tile(tile + 4);
-        consume(t1, tile + 1);
-        if (tile + 2 >= ntile) break;
-        t1 = load_tile(tile + 5);
-        consume(t2, tile + 2);
-        if (tile + 3 >= ntile) break;
-        t2 = load_tile(tile + 6);
-        consume(t3, tile + 3);
+        for (int tile = 0; tile < ntile; tile += 3) {
+          Tile t2 = load_tile(tile + 2);
+          consume(t0, tile);
+          if (tile + 1 >= ntile) break;
+          t0 = load_tile(tile + 3);
+          consume(t1, tile + 1);
+          if (tile + 2 >= ntile) break;
+          t1 = load_tile(tile + 4);
+          consume(t2, tile + 2);
+        }
       }
-#else
-      Tile cur = load_tile(0);
-#pragma unroll 1
-      for (int tile = 0; tile < ntile; ++tile) {
-        const Tile nxt = load_tile(tile + 1);  // zeros past the end
-        consume(cur, tile);
-        cur = nxt;
-      }
-#endif
       if (!a.dense || kPaged) __syncthreads();  // the next sub-range rewrites the row table
     }
 
     // ---- merge the lane-group states: common max, rescale, sum
-    if (sl == hl * (16 / G)) {
+    if (sl == (kMatrix ? hl : hl * (16 / G))) {
       s_ml[gid][0][hl] = m;
       s_ml[gid][1][hl] = l;
     }
@@ -487,11 +615,12 @@ void attn_splitk_kernel(AttnArgs a) {
       // outputs per thread summed over the NG lane-groups
 #pragma unroll
       for (int h = 0; h < G; ++h) {
-        const float sc = head_value<G>(sc_own, h);
+        const float sc = of_head(sc_own, h);
 #pragma unroll
         for (int e = 0; e < EPL; e += 4)
           *reinterpret_cast<float4*>(&s_red[gid][h][sl * EPL + e]) =
-              make_float4(acc[h][e] * sc, acc[h][e + 1] * sc, acc[h][e + 2] * sc, acc[h][e + 3] * sc);
+              make_float4(accv[h / 4][e][h % 4] * sc, accv[h / 4][e + 1][h % 4] * sc, accv[h / 4][e + 2][h % 4] * sc,
+                          accv[h / 4][e + 3][h % 4] * sc);
       }
       __syncthreads();
       if (tid * 4 < G * kHeadDim) {
@@ -510,20 +639,20 @@ void attn_splitk_kernel(AttnArgs a) {
     } else {
 #pragma unroll
       for (int h = 0; h < G; ++h) {
-        const float sc = head_value<G>(sc_own, h);
+        const float sc = of_head(sc_own, h);
 #pragma unroll
         for (int e = 0; e < EPL; ++e) {
-          float v = acc[h][e] * sc;
+          float v = accv[h / 4][e][h % 4] * sc;
           v += __shfl_xor(v, 16, 64);
           v += __shfl_xor(v, 32, 64);
-          acc[h][e] = v;
+          accv[h / 4][e][h % 4] = v;
         }
       }
       if (grp == 0) {
 #pragma unroll
         for (int h = 0; h < G; ++h)
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) s_red[wave][h][sl * EPL + e] = acc[h][e];
+          for (int e = 0; e < EPL; ++e) s_red[wave][h][sl * EPL + e] = accv[h / 4][e][h % 4];
       }
       __syncthreads();
       for (int i = tid; i < G * kHeadDim; i += 256) {
@@ -627,13 +756,12 @@ static size_t attn_dyn_lds(const AttnArgs& a) { return ((size_t)a.B * a.NV + 1) 
 
 template <bool kPaged>
 static hipError_t launch_attn_t(const AttnArgs& a, int G, int grid, hipStream_t st) {
-  constexpr int TOK = TACTIC_ATTN_TOK;
   const size_t lds = attn_dyn_lds(a);
   switch (G) {
-    case 1: hipLaunchKernelGGL((attn_splitk_kernel<1, TOK, kPaged>), dim3(grid), dim3(256), lds, st, a); break;
-    case 2: hipLaunchKernelGGL((attn_splitk_kernel<2, TOK, kPaged>), dim3(grid), dim3(256), lds, st, a); break;
-    case 4: hipLaunchKernelGGL((attn_splitk_kernel<4, TOK, kPaged>), dim3(grid), dim3(256), lds, st, a); break;
-    case 8: hipLaunchKernelGGL((attn_splitk_kernel<8, TOK, kPaged>), dim3(grid), dim3(256), lds, st, a); break;
+    case 1: hipLaunchKernelGGL((attn_splitk_kernel<1, attn_tok(1), kPaged>), dim3(grid), dim3(256), lds, st, a); break;
+    case 2: hipLaunchKernelGGL((attn_splitk_kernel<2, attn_tok(2), kPaged>), dim3(grid), dim3(256), lds, st, a); break;
+    case 4: hipLaunchKernelGGL((attn_splitk_kernel<4, attn_tok(4), kPaged>), dim3(grid), dim3(256), lds, st, a); break;
+    case 8: hipLaunchKernelGGL((attn_splitk_kernel<8, attn_tok(8), kPaged>), dim3(grid), dim3(256), lds, st, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -648,12 +776,11 @@ hipError_t launch_attn(const AttnArgs& a, int G, int grid, bool paged, hipStream
 // share of the tokens from the start.
 template <bool kPaged>
 static hipError_t resident_t(int G, size_t lds, int* per) {
-  constexpr int TOK = TACTIC_ATTN_TOK;
   switch (G) {
-    case 1: return hipOccupancyMaxActiveBlocksPerMultiprocessor(per, attn_splitk_kernel<1, TOK, kPaged>, 256, lds);
-    case 2: return hipOccupancyMaxActiveBlocksPerMultiprocessor(per, attn_splitk_kernel<2, TOK, kPaged>, 256, lds);
-    case 4: return hipOccupancyMaxActiveBlocksPerMultiprocessor(per, attn_splitk_kernel<4, TOK, kPaged>, 256, lds);
-    case 8: return hipOccupancyMaxActiveBlocksPerMultiprocessor(per, attn_splitk_kernel<8, TOK, kPaged>, 256, lds);
+    case 1: return hipOccupancyMaxActiveBlocksPerMultiprocessor(per, attn_splitk_kernel<1, attn_tok(1), kPaged>, 256, lds);
+    case 2: return hipOccupancyMaxActiveBlocksPerMultiprocessor(per, attn_splitk_kernel<2, attn_tok(2), kPaged>, 256, lds);
+    case 4: return hipOccupancyMaxActiveBlocksPerMultiprocessor(per, attn_splitk_kernel<4, attn_tok(4), kPaged>, 256, lds);
+    case 8: return hipOccupancyMaxActiveBlocksPerMultiprocessor(per, attn_splitk_kernel<8, attn_tok(8), kPaged>, 256, lds);
     default: return hipErrorInvalidValue;
   }
 }
