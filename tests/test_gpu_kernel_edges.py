@@ -1,0 +1,192 @@
+"""Kernel variants at the sizes where their dispatch or tiling changes."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _T():
+    import paper_2502_12216_amd as T
+    return T
+
+
+def _keys(h, n, kind, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    if kind == "ties":  # small integers: many exactly equal distances
+        K = torch.zeros(h, n, 128, device="cuda")
+        K[..., :4] = torch.randint(-1, 2, (h, n, 4), generator=g, device="cuda").float()
+    else:
+        c = torch.randn(h, max(1, n // 16), 128, generator=g, device="cuda")
+        lab = torch.randint(0, c.shape[1], (h, n), generator=g, device="cuda")
+        K = torch.stack([c[i][lab[i]] for i in range(h)]) + 0.3 * torch.randn(h, n, 128, generator=g, device="cuda")
+    return K.to(torch.bfloat16).contiguous()
+
+
+@pytest.mark.parametrize("kind", ["mixture", "ties"])
+@pytest.mark.parametrize("lens,ncl", [([300], [18]), ([2049, 255, 256], [129, 16, 16]), ([5000, 600], [4, 97]),
+                                      ([9000], [1]), ([20011], [1250])])
+def test_kmeans_later_iterations_equal_full_steps(lens, ncl, kind):
+    """An iteration after the first measures only pairs whose centroid changed; a
+    call of one iteration measures every pair.  Chained through the warm start,
+    t such calls must give bit for bit what one call of t iterations gives
+    (member lists in LDS, of more than 64 members, and in memory)."""
+    T = _T()
+    h = 2
+    K, V = _keys(h, sum(lens), kind, 1), _keys(h, sum(lens), "mixture", 2)
+    rng = np.random.default_rng(3)
+    init = torch.as_tensor(np.concatenate([np.stack([rng.choice(n, c, replace=False) for _ in range(h)])
+                                           for n, c in zip(lens, ncl)], 1).astype(np.int32), device="cuda")
+    batch = T.RaggedBatch(lens, h, h)
+    one = T.ClusterBuilder(batch, ncl, max_iters=1)
+    prev = None
+    for t in range(1, 7):
+        step = one(K, V, init, prev=prev)
+        many = T.ClusterBuilder(batch, ncl, max_iters=t)
+        many.workspace.fill_(0xA5)  # contents on entry are irrelevant
+        got = many(K, V, init)
+        for name, x, y in (("assign", got.assign, step.assign), ("offsets", got.clusters.offsets, step.clusters.offsets),
+                           ("perm", got.perm, step.perm),
+                           ("centroids", got.clusters.centroids.view(torch.int16), step.clusters.centroids.view(torch.int16)),
+                           ("K_sorted", got.K_sorted.view(torch.int16), step.K_sorted.view(torch.int16))):
+            assert torch.equal(x, y), f"{name} after {t} iterations"
+        prev = step.clusters
+
+
+def _decode(lens, ncl, hq, hkv, seed, sizes=None, union=1, target=0.9):
+    """A sparse decode over random keys with the given cluster sizes (default: even, some empty)."""
+    T = _T()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    rng = np.random.default_rng(seed)
+    total = sum(lens)
+    K = torch.randn(hkv, total, 128, generator=g, device="cuda").to(torch.bfloat16)
+    V = torch.randn(hkv, total, 128, generator=g, device="cuda").to(torch.bfloat16)
+    cen = torch.randn(hkv, sum(ncl), 128, generator=g, device="cuda").to(torch.bfloat16)
+    off = []
+    for n, c in zip(lens, ncl):
+        cuts = np.sort(rng.integers(0, n + 1, size=(hkv, c - 1)), axis=1) if sizes is None else \
+            np.tile(np.cumsum(sizes)[:-1], (hkv, 1))
+        off.append(np.concatenate([np.zeros((hkv, 1), np.int64), cuts, np.full((hkv, 1), n)], 1))
+    offs = np.concatenate(off, 1).astype(np.int32)
+    batch = T.RaggedBatch(lens, hq, hkv)
+    dec = T.SparseDecoder(batch, ncl, T.decode_params(target, use_union=union))
+    q = (0.3 * torch.randn(len(lens), hq, 128, generator=g, device="cuda")).to(torch.bfloat16)
+    out, sq, skv = dec(q, K, V, T.ClusterSet(cen, torch.as_tensor(offs, device="cuda"), ncl))
+    torch.cuda.synchronize()
+    return dict(q=q, K=K, V=V, off=off, out=out, sq=sq.cpu().numpy(), skv=skv.cpu().numpy(),
+                view={k: v.cpu().numpy() for k, v in dec.view().items()}, batch=batch)
+
+
+def _positions(n):
+    """Sampled positions (1-based) of a list of n tokens, default parameters."""
+    N = min(n, max(1, -(-n // 100)))
+    W = max(8, -(-n * 50 // 10000))
+    s1 = max((n * 1000 + 5000) // 10000 - W // 2, N + 1)
+    s2 = max((n * 6000 + 5000) // 10000 - W // 2, N + 1)
+    t1, t2 = min(s1 + W - 1, n), min(s2 + W - 1, n)
+    if N == n or s1 > t1 or s2 > t2 or t1 >= s2:
+        return np.arange(1, n + 1)
+    return np.concatenate([np.arange(1, N + 1), np.arange(s1, t1 + 1), np.arange(s2, t2 + 1)])
+
+
+def _check_selection(r, lens, ncl, hq, hkv, union=1):
+    G = hq // hkv
+    v, c0 = r["view"], 0
+    for b, (n, C) in enumerate(zip(lens, ncl)):
+        lengths = np.zeros((hq, C), np.int64)
+        for h in range(hq):
+            off = r["off"][b][h // G]
+            size = np.diff(off)
+            order = np.lexsort((np.arange(C), -v["scores"][b, h, :C]))
+            assert np.array_equal(v["order"][b, h, :C], order), (b, h)
+            pre = np.concatenate([[0], np.cumsum(size[order])])
+            assert np.array_equal(v["rank_prefix"][b, h, :C + 1], pre), (b, h)
+            pos = _positions(n)
+            rank = np.searchsorted(pre, pos, side="left") - 1  # the largest rank with fewer tokens ahead
+            rows = off[order[rank]] + pos - 1 - pre[rank]
+            assert np.array_equal(v["sample_rows"][b, h, :len(pos)], rows), (b, h)
+            k = int(r["sq"][b, h])
+            lengths[h, order] = np.minimum(np.maximum(k - pre[:-1], 0), size[order])
+        groups = [range(g * G, (g + 1) * G) for g in range(hkv)] if union else [[h] for h in range(hq)]
+        for j, heads in enumerate(groups):
+            want = lengths[list(heads)].max(0)
+            assert np.array_equal(v["union_len"][j, c0:c0 + C], want), (b, j)
+            if union:
+                assert r["skv"][b, j] == want.sum()
+        c0 += C
+
+
+@pytest.mark.parametrize("C", [1, 1024, 1025, 2049, 4096, 4097, 8192, 8193, 16384, 16385, 20001])
+def test_sort_at_slot_edges(C):
+    """Slots per thread of the LDS sort (1024, 2048, 4096, 8192 and 16384 clusters), and the pieces beyond."""
+    lens, ncl = [max(1, 2 * C + 7), 33], [C, 5]
+    _check_selection(_decode(lens, ncl, 4, 1, C), lens, ncl, 4, 1)
+
+
+def test_sort_two_heads_per_compute_unit():
+    """More than 256 heads of up to 8192 clusters: slots by each head's own count."""
+    ncl = [4100, 8192, 1, 700, 1500, 3000, 4096, 5000, 1024]
+    lens = [2 * c + 11 for c in ncl]
+    _check_selection(_decode(lens, ncl, 32, 8, 5), lens, ncl, 32, 8)
+
+
+@pytest.mark.parametrize("C,big", [(9, 1 << 19), (8193, 1 << 18), (20001, 70000)])
+def test_sort_cluster_sizes_beyond_the_packed_word(C, big):
+    sizes = np.ones(C, np.int64)
+    sizes[C // 2] = big
+    lens, ncl = [int(sizes.sum())], [C]
+    _check_selection(_decode(lens, ncl, 2, 1, 9, sizes=sizes), lens, ncl, 2, 1)
+
+
+@pytest.mark.parametrize("C", [6143, 6144, 6145, 13000])
+@pytest.mark.parametrize("target", [0.3, 0.97])
+def test_union_of_eight_heads(C, target):
+    """One workgroup up to 6144 clusters, slices beyond."""
+    lens, ncl = [3 * C, 40], [C, 6]
+    _check_selection(_decode(lens, ncl, 8, 1, C, target=target), lens, ncl, 8, 1)
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 63, 64, 65, 127, 255, 513, 4099])
+@pytest.mark.parametrize("paged", [False, True])
+def test_eight_head_attention_tile_remainders(n, paged):
+    """Dense decode of 8 heads per KV head (matrix form, tiles of 64 tokens).  Bound: fp32 logits (error at
+    most a few ulp of sum |q_i k_i| / sqrt(128), here below 30: 1e-5 relative in a weight)."""
+    T = _T()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    lens = [n, 70]
+    K = torch.randn(2, sum(lens), 128, generator=g, device="cuda").to(torch.bfloat16)
+    V = torch.randn(2, sum(lens), 128, generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn(2, 16, 128, generator=g, device="cuda").to(torch.bfloat16)
+    batch = T.RaggedBatch(lens, 16, 2)
+    dec = T.DenseDecoder(batch)
+    out = dec.paged(q, T.PagedCache.from_token_order(K, V, batch, 16)) if paged else dec(q, K, V)
+    s = 0
+    for b, m in enumerate(lens):
+        for h in range(16):
+            k, v = K[h // 8, s:s + m].double(), V[h // 8, s:s + m].double()
+            ref = torch.softmax(k @ q[b, h].double() / 128 ** 0.5, 0) @ v
+            assert (out[b, h].double() - ref).abs().max() <= 1e-5 * max(1.0, float(v.abs().max()))
+        s += m
+
+
+def test_eight_head_attention_infinite_values():
+    """An infinite value reaches the heads that give its token any weight as that infinity, and a weight that is
+    exactly zero times it is NaN: as with one multiplication per weight."""
+    T = _T()
+    n = 200
+    K = torch.zeros(1, n, 128, dtype=torch.bfloat16, device="cuda")
+    V = torch.ones(1, n, 128, dtype=torch.bfloat16, device="cuda")
+    V[0, 17, 3] = float("inf")
+    V[0, 150, 5] = float("-inf")
+    K[0, 17, 0] = -100.0  # head 1 below: weight 2^-inf
+    q = torch.zeros(1, 8, 128, dtype=torch.bfloat16, device="cuda")
+    q[0, 1, 0] = 1000.0
+    out = T.DenseDecoder(T.RaggedBatch([n], 8, 1))(q, K, V)[0].cpu()
+    for h in range(8):
+        assert out[h, 5] == -float("inf")
+        assert torch.isnan(out[h, 3]) if h == 1 else out[h, 3] == float("inf")
+        rest = torch.cat([out[h, :3], out[h, 4:5], out[h, 6:]])
+        assert torch.allclose(rest, torch.ones_like(rest), atol=1e-5)
