@@ -168,11 +168,17 @@ __global__ __launch_bounds__(256) void km_init_kernel(KmArgs a) {
 // finished scores and the epilogue is the maximum over each lane's 16
 // scores of a block (by groups of four), and the search for the row that holds
 // it, and for the second largest of the 16, only when some lane of the wave
-// improved on its best (strict, so the smaller row wins a tie).  The second
-// best score over all rows seen costs one median per block outside of that
-// search.
+// improved on its best (strict, so the smaller row wins a tie).  kTrack: also
+// the second best score over all rows seen, for the keys' bounds.
 //
-// kMode 0 (first iteration): every key against every centroid.
+// kMode 0: every key against every centroid.  From sampled keys almost every
+//   centroid moves in the first update (97% on a mixture), so the second
+//   iteration measures every pair as well, and only that pass tracks the second
+//   best (131072 x 4 sequences x 8 heads, 8192 clusters: 7.1 ms per pass, 9.2
+//   with it, 8.4 for the second iteration as kMode 1 and 2; 65536 x 8, two
+//   iterations 1.37 -> 1.26 ms, ten 2.35 -> 2.26).  From a previous clustering
+//   the first pass tracks it and pruning starts at once (two iterations 1.03 ms
+//   against 1.26); a call that ends with the full passes does not track.
 // kMode 1: every key against the rows of d_rows.  The search starts from a
 //   score that a new best must exceed: the key's bound where its own centroid
 //   changed (the unchanged ones do not exceed it), else the value just below
@@ -205,8 +211,9 @@ __device__ __forceinline__ float second_of4(float a, float b, float c, float d) 
 }
 
 // three waves per SIMD: the B operands and accumulators live in VGPRs
-template <int kMode>
+template <int kMode, bool kTrack = true>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void km_assign_kernel(KmArgs a) {
+  static_assert(kTrack || kMode == 0, "only full passes go without bounds");
   // two centroid tiles (the next one loads while this one is contracted):
   // rows of 16 chunks of 16 bytes, logical chunk c of row r stored at chunk
   // c ^ (r & 15), so that the 32 rows an A-operand read touches at one
@@ -218,6 +225,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   if (*done_flag(a, p)) return;
   const int nd = kMode == 1 ? *n_moved(a, p) : 0, nl = kMode == 2 ? *n_listed(a, p) : 0;
   if (kMode == 1 && nd == 0) return;  // no centroid changed: no key does
+  if (kMode == 0 && a.iter > 1 && *n_moved(a, p) == 0) return;
   if (kMode == 2 && nl == 0) return;
   const Problem q = problem(a, p);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -226,7 +234,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   const int slices = kMode == 2 ? (q.C + kListCen - 1) / kListCen : 1;
   const uint16_t* cbase = (kMode == 1 ? a.d_rows : a.centroids) + q.cl_base * kHeadDim;
   const float* cnorm = (kMode == 1 ? a.d_norm : a.cnorm) + q.cl_base;
-  if (kMode == 1 && tid < 3) s_n[tid] = 0;  // (the tile loop's barriers order it before its use)
+  if (kMode < 2 && tid < 3) s_n[tid] = 0;  // (the tile loop's barriers order it before its use)
   for (int64_t item = blockIdx.x;; item += gridDim.x) {  // kMode 0, 1: one item
     const int64_t first = (kMode == 2 ? item / slices : item) * kAsgTok;
     const int c_beg = kMode == 2 ? (int)(item % slices) * kListCen : 0;
@@ -320,17 +328,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             for (int j = 0; j < 4; ++j) x[j] = e0 ? v[j] : (e1 ? v[4 + j] : (e2 ? v[8 + j] : v[12 + j]));
             int r = e0 ? 0 : (e1 ? 8 : (e2 ? 16 : 24));
             r += x[0] == mx ? 0 : (x[1] == mx ? 1 : (x[2] == mx ? 2 : 3));
-            const float s2 = fmaxf(second_of4(g[0], g[1], g[2], g[3]), second_of4(x[0], x[1], x[2], x[3]));
-            // not improved: the block's maximum is a candidate for the second
-            sec_v[bb] = imp ? fmaxf(best_v[bb], s2) : fmaxf(sec_v[bb], mx);
+            if (kTrack) {
+              const float s2 = fmaxf(second_of4(g[0], g[1], g[2], g[3]), second_of4(x[0], x[1], x[2], x[3]));
+              // not improved: the block's maximum is a candidate for the second
+              sec_v[bb] = imp ? fmaxf(best_v[bb], s2) : fmaxf(sec_v[bb], mx);
+            }
             best_v[bb] = imp ? mx : best_v[bb];
             best_j[bb] = imp ? c0 + cb * 32 + 4 * half + r : best_j[bb];
-          } else {
+          } else if (kTrack) {
             sec_v[bb] = fmaxf(sec_v[bb], mx);
           }
         }
       }
     }
+    if (kMode == 0) __syncthreads();  // (s_n is cleared where no tile was loaded, too)
 #pragma unroll
     for (int bb = 0; bb < 2; ++bb) {
       const float ov = __shfl_xor(best_v[bb], 32, 64), os = __shfl_xor(sec_v[bb], 32, 64);
@@ -345,11 +356,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       const int i = i0 + wave * 64 + bb * 32 + col;
       const bool own = half == 0 && i < m;
       const int64_t at = q.tok_base + (kMode == 2 ? tokv[bb] : i);
-      if (kMode == 0 && own) {
-        const int jn = min(max(best_j[bb], 0), q.C - 1);
-        a.assign[at] = jn;
-        a.best[at] = best_v[bb];
-        a.bound[at] = sec;
+      if (kMode == 0) {
+        bool changed = false;
+        if (own) {
+          const int jn = min(max(best_j[bb], 0), q.C - 1);
+          const int old = a.iter > 1 ? a.assign[at] : jn;
+          changed = jn != old;
+          if (changed) {
+            a.dirty[q.cl_base + old] = 1;
+            a.dirty[q.cl_base + jn] = 1;
+          }
+          if (changed || a.iter == 1) a.assign[at] = jn;
+          if (kTrack) {
+            a.best[at] = best_v[bb];
+            a.bound[at] = sec;
+          }
+        }
+        const uint64_t cm = __ballot(changed);
+        if (cm && lane == 0) atomicAdd(&s_n[1], (int)__popcll(cm));
       }
       if (kMode == 1) {
         bool listed = false, changed = false;
@@ -410,6 +434,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       }
     }
     if (kMode != 2) break;
+  }
+  if (kMode == 0 && a.iter > 1) {
+    __syncthreads();
+    if (tid == 0 && s_n[1]) atomicAdd(n_changed(a, p), s_n[1]);
   }
   if (kMode == 1) {
     __syncthreads();
@@ -1086,10 +1114,12 @@ hipError_t run_kmeans(const uint16_t* K, const uint16_t* V, const int64_t* kv_in
   const dim3 g_list((unsigned)std::min<int64_t>(items, std::max(8, 768 / BG)), BG);
   hipLaunchKernelGGL(km_init_kernel, g_cl, dim3(256), 0, st, a);
   hipError_t e = hipGetLastError();
+  const int full = a.prev_centroids ? 1 : 2;  // iterations that measure every pair; the last of them leaves the bounds
   for (int it = 1; it <= max_iters && e == hipSuccess; ++it) {
     a.iter = it;
-    if (it == 1) {
-      hipLaunchKernelGGL(km_assign_kernel<0>, g_tok, dim3(256), 0, st, a);
+    if (it <= full) {
+      if (it == full && max_iters > full) hipLaunchKernelGGL((km_assign_kernel<0, true>), g_tok, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((km_assign_kernel<0, false>), g_tok, dim3(256), 0, st, a);
     } else {
       hipLaunchKernelGGL(km_assign_kernel<1>, g_tok, dim3(256), 0, st, a);
       hipLaunchKernelGGL(km_assign_kernel<2>, g_list, dim3(256), 0, st, a);
