@@ -174,11 +174,11 @@ __global__ __launch_bounds__(256) void km_init_kernel(KmArgs a) {
 // kMode 0: every key against every centroid.  From sampled keys almost every
 //   centroid moves in the first update (97% on a mixture), so the second
 //   iteration measures every pair as well, and only that pass tracks the second
-//   best (131072 x 4 sequences x 8 heads, 8192 clusters: 7.1 ms per pass, 9.2
-//   with it, 8.4 for the second iteration as kMode 1 and 2; 65536 x 8, two
-//   iterations 1.37 -> 1.26 ms, ten 2.35 -> 2.26).  From a previous clustering
-//   the first pass tracks it and pruning starts at once (two iterations 1.03 ms
-//   against 1.26); a call that ends with the full passes does not track.
+//   best (131072 x 4 sequences x 8 heads, 8192 clusters: first iteration 8.4
+//   ms, 9.2 with it; second 8.3 ms, 8.4 as kMode 1 and 2 behind a tracked first;
+//   65536 x 8, two iterations 1.37 -> 1.26 ms, ten 2.35 -> 2.26).  From a
+//   previous clustering the first pass tracks it and pruning starts at once
+//   (two iterations 1.03 ms); a call that ends with the full passes does not track.
 // kMode 1: every key against the rows of d_rows.  The search starts from a
 //   score that a new best must exceed: the key's bound where its own centroid
 //   changed (the unchanged ones do not exceed it), else the value just below
