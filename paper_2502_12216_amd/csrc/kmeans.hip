@@ -201,9 +201,12 @@ __device__ __forceinline__ uint32_t score_key(float s) {  // ascending with s, n
 __device__ __forceinline__ float key_to_score(uint32_t k) {  // 0 (no score): -inf
   return k == 0 ? -INFINITY : __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
-__device__ __forceinline__ float just_below(float s) {  // the next smaller float (-inf stays)
+// A float below s with no value between (-inf stays).  Below 0 it is the largest
+// negative one, not -0, which compares equal: the key before that of 0 stands for
+// no value (score_key reads -0 as 0).
+__device__ __forceinline__ float just_below(float s) {
   const uint32_t k = score_key(s);
-  return s == -INFINITY ? s : key_to_score(k - 1);
+  return s == -INFINITY ? s : key_to_score(k - (s == 0.0f ? 2u : 1u));
 }
 __device__ __forceinline__ float second_of4(float a, float b, float c, float d) {
   const float h0 = fmaxf(a, b), l0 = fminf(a, b), h1 = fmaxf(c, d), l1 = fminf(c, d);

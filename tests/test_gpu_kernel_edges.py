@@ -54,6 +54,32 @@ def test_kmeans_later_iterations_equal_full_steps(lens, ncl, kind):
         prev = step.clusters
 
 
+def _cluster_set(cen, ncl):
+    off = torch.zeros(cen.shape[0], sum(ncl) + len(ncl), dtype=torch.int32, device="cuda")
+    return _T().ClusterSet(cen, off, ncl)
+
+
+def test_kmeans_equal_scores_of_zero():
+    """A key whose own, unmoved centroid scores exactly 0 and a centroid of smaller id that moved and scores 0 too
+    goes to the smaller id (two dimensions, the rest zero, every value exact in bf16).  From c0 = (1, -1.5) and
+    c1 = (1, 1) the first step assigns (1, 0), (1, 2), (1, -1) to 1, 1, 0; c0 moves to (1, -1), c1 stays; then
+    (1, 0) scores 1 - (1 + 1) / 2 = 0 with both."""
+    T = _T()
+
+    def rows(x):
+        t = torch.zeros(1, len(x), 128, device="cuda")
+        t[0, :, :2] = torch.tensor(x, device="cuda")
+        return t.to(torch.bfloat16)
+
+    K = rows([[1.0, 0.0], [1.0, 2.0], [1.0, -1.0]])
+    prev = _cluster_set(rows([[1.0, -1.5], [1.0, 1.0]]), [2])
+    init = torch.zeros(1, 2, dtype=torch.int32, device="cuda")
+    got = T.ClusterBuilder(T.RaggedBatch([3], 1, 1), [2], max_iters=10)(K, K, init, prev=prev)
+    assert got.assign.tolist() == [[0, 1, 0]]
+    assert torch.equal(got.clusters.centroids, rows([[1.0, -0.5], [1.0, 2.0]]))
+    assert got.perm.tolist() == [[0, 2, 1]] and got.clusters.offsets.tolist() == [[0, 2, 3]]
+
+
 def _decode(lens, ncl, hq, hkv, seed, sizes=None, union=1, target=0.9):
     """A sparse decode over random keys with the given cluster sizes (default: even, some empty)."""
     T = _T()
