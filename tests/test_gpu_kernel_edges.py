@@ -17,6 +17,9 @@ def _keys(h, n, kind, seed):
     if kind == "ties":  # small integers: many exactly equal distances
         K = torch.zeros(h, n, 128, device="cuda")
         K[..., :4] = torch.randint(-1, 2, (h, n, 4), generator=g, device="cuda").float()
+    elif kind == "zeros":  # half of the keys are zero: one cluster of thousands of keys
+        K = torch.randn(h, n, 128, generator=g, device="cuda")
+        K[torch.rand(h, n, generator=g, device="cuda") < 0.5] = 0.0
     else:
         c = torch.randn(h, max(1, n // 16), 128, generator=g, device="cuda")
         lab = torch.randint(0, c.shape[1], (h, n), generator=g, device="cuda")
@@ -24,14 +27,18 @@ def _keys(h, n, kind, seed):
     return K.to(torch.bfloat16).contiguous()
 
 
-@pytest.mark.parametrize("kind", ["mixture", "ties"])
+@pytest.mark.parametrize("warm", [False, True])
+@pytest.mark.parametrize("kind", ["mixture", "ties", "zeros"])
 @pytest.mark.parametrize("lens,ncl", [([300], [18]), ([2049, 255, 256], [129, 16, 16]), ([5000, 600], [4, 97]),
-                                      ([9000], [1]), ([20011], [1250])])
-def test_kmeans_later_iterations_equal_full_steps(lens, ncl, kind):
-    """An iteration after the first measures only pairs whose centroid changed; a
-    call of one iteration measures every pair.  Chained through the warm start,
-    t such calls must give bit for bit what one call of t iterations gives
-    (member lists in LDS, of more than 64 members, and in memory)."""
+                                      ([9000], [1]), ([20011], [1250]), ([33001, 17000], [3, 40])])
+def test_kmeans_later_iterations_equal_full_steps(lens, ncl, kind, warm):
+    """A later iteration measures only pairs whose centroid changed (from the third
+    on, from the second of a warm start, which begins from the centroids of
+    other keys, so that most of them move); a call of one iteration measures
+    every pair.  Chained through the warm start, t such calls must give bit
+    for bit what one call of t iterations gives (member lists in LDS, of more
+    than 64 members, and in memory, there also of more than 256 among more
+    than 16384 tokens)."""
     T = _T()
     h = 2
     K, V = _keys(h, sum(lens), kind, 1), _keys(h, sum(lens), "mixture", 2)
@@ -40,18 +47,45 @@ def test_kmeans_later_iterations_equal_full_steps(lens, ncl, kind):
                                            for n, c in zip(lens, ncl)], 1).astype(np.int32), device="cuda")
     batch = T.RaggedBatch(lens, h, h)
     one = T.ClusterBuilder(batch, ncl, max_iters=1)
-    prev = None
+    start = _cluster_set(V[:, :sum(ncl)].contiguous(), ncl) if warm else None
+    prev = start
     for t in range(1, 7):
         step = one(K, V, init, prev=prev)
         many = T.ClusterBuilder(batch, ncl, max_iters=t)
         many.workspace.fill_(0xA5)  # contents on entry are irrelevant
-        got = many(K, V, init)
+        got = many(K, V, init, prev=start)
         for name, x, y in (("assign", got.assign, step.assign), ("offsets", got.clusters.offsets, step.clusters.offsets),
                            ("perm", got.perm, step.perm),
                            ("centroids", got.clusters.centroids.view(torch.int16), step.clusters.centroids.view(torch.int16)),
                            ("K_sorted", got.K_sorted.view(torch.int16), step.K_sorted.view(torch.int16))):
             assert torch.equal(x, y), f"{name} after {t} iterations"
         prev = step.clusters
+
+
+@pytest.mark.parametrize("n,C", [(700, 3), (5001, 300), (20011, 4), (20011, 200), (70000, 2), (270001, 5)])
+@pytest.mark.parametrize("kind", ["mixture", "zeros"])
+def test_kmeans_one_step_layout_and_means(n, C, kind):
+    """One iteration: the layout is the stable order of the assignment, bit for bit, and every mean is that of the
+    cluster's keys, summed in four interleaved chains (a bound of the fp32 sums: members / 4 + 2 additions, each
+    2^-24 of the sum of magnitudes, then a factor and a rounding to bf16, 2^-8 with a margin of 2^-20)."""
+    T = _T()
+    K = _keys(1, n, kind, n + C)
+    rng = np.random.default_rng(n)
+    init = torch.as_tensor(rng.choice(n, C, replace=False).astype(np.int32)[None], device="cuda")
+    r = T.ClusterBuilder(T.RaggedBatch([n], 1, 1), [C], max_iters=1)(K, K, init)
+    a = r.assign[0].long()
+    assert torch.equal(r.perm[0].long(), torch.sort(a, stable=True).indices)
+    cnt = torch.bincount(a, minlength=C)
+    assert torch.equal(r.clusters.offsets[0].long()[1:], torch.cumsum(cnt, 0))
+    assert torch.equal(r.K_sorted[0], K[0][r.perm[0].long()])
+    s = torch.zeros(C, 128, dtype=torch.float64, device="cuda").index_add_(0, a, K[0].double())
+    m = torch.zeros(C, 128, dtype=torch.float64, device="cuda").index_add_(0, a, K[0].double().abs())
+    full = cnt > 0
+    c = cnt[full, None].double()
+    mean, err = s[full] / c, m[full] / c * (c / 4 + 3) * 2.0 ** -24
+    got = r.clusters.centroids[0][full].double()
+    assert torch.all((got - mean).abs() <= err + (mean.abs() + err) * (2.0 ** -8 + 2.0 ** -20))
+    assert torch.equal(r.clusters.centroids[0][~full], K[0][init[0].long()][~full])
 
 
 def _cluster_set(cen, ncl):
