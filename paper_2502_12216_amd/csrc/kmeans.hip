@@ -20,8 +20,8 @@
 //               (fixed, so results are deterministic), rounded to bf16; an empty
 //               cluster keeps its centroid.  Centroids that changed are copied
 //               to the next iteration's list.
-// After the last iteration km_layout counts the clusters and places every token
-// by its rank, and the K/V rows are permuted into cluster order.
+// After the last iteration km_layout scans the clusters' sizes, and km_permute puts
+// every token and its K/V rows at its cluster's start plus its rank.
 //
 // Measured on keys of a 4096-component mixture (65536 x 8 heads, 10
 // iterations): the changed centroids are 97, 56, 17, 3, 0.8 ... % of all from the
@@ -41,11 +41,11 @@ namespace tactic {
 constexpr int kAsgTok = 256;        // tokens per assignment workgroup (4 waves x 64)
 constexpr int kAsgCen = 96;         // centroids staged in LDS per step
 constexpr int kListCen = 2 * kAsgCen;  // centroids per work item of the listed keys
-constexpr int kSliceMax = 4096;     // clusters per slice of the update and layout kernels
-constexpr int kSliceCap = 4096;     // keys per slice that they collect in LDS
-constexpr int kRankMax = 256;       // members ranked by counting in LDS; beyond, by a bitmap of tokens
+constexpr int kSliceMax = 2048;     // clusters per slice of the update kernel
+constexpr int kSliceCap = 4096;     // keys per slice that it collects in LDS
+constexpr int kRankMax = 256;       // members that one wave ranks, of a slice with lists in memory
 constexpr int kOrdWords = 512;      // words of LDS per wave for sorting members
-constexpr int kBitTokens = kOrdWords * 32;  // tokens per bitmap window
+constexpr int kBitTokens = 16 * kOrdWords * 32;  // tokens per bitmap window of a workgroup
 constexpr int kSmall = 64;          // members of a cluster that one wave takes in one go
 constexpr int kStateInts = 64;      // counters of a problem, each in a 64-byte line of its own
 
@@ -107,6 +107,35 @@ __device__ __forceinline__ Problem problem(const KmArgs& a, int p) {
   q.cl_base = (int64_t)q.g * a.Ct + c0;
   q.off_base = (int64_t)q.g * (a.Ct + a.B) + c0 + q.b;
   return q;
+}
+
+// A slice of a problem's clusters: those whose bit-reversed id lies in [lo, lo + nr),
+// local index j standing for reversed id lo + j (at most about half of them are
+// ids past the last cluster).  Of equal keys the smallest id takes all: 81
+// distinct keys in 65536, 4096 clusters, had 64 of their clusters in the first 128 ids,
+// and one workgroup 52000 keys to gather; bit reversal spreads any run of ids
+// evenly, for one instruction per key.
+struct Slice {
+  int lo, nr, shift, C;
+  __device__ __forceinline__ int id(int j) const { return (int)__brev((uint32_t)(lo + j) << shift); }  // (>= C: none)
+  // place of cluster c on the scale of the reversed ids from the slice's start (c < 0: in no slice)
+  __device__ __forceinline__ uint32_t place(int c) const {
+    return c < 0 ? 0xffffffffu : __brev((uint32_t)c) - ((uint32_t)lo << shift);
+  }
+  // places below are in the slice (a place's low bits are 0: one less keeps a slice of all ids in 32 bits)
+  __device__ __forceinline__ uint32_t end() const { return ((uint32_t)nr << shift) - 1u; }
+  __device__ __forceinline__ int local(uint32_t place) const { return (int)(place >> shift); }
+};
+
+// slice s of at most `per` clusters on average: nr <= 2 per (2^bits < 2 C), 0 past the last slice
+__device__ __forceinline__ Slice make_slice(int C, int per, int s) {
+  Slice x;
+  const int ns = (C + per - 1) / per, bits = C > 2 ? 32 - __clz(C - 1) : 1;
+  x.C = C;
+  x.shift = 32 - bits;
+  x.lo = s < ns ? (int)(((int64_t)s << bits) / ns) : 0;
+  x.nr = s < ns ? (int)(((int64_t)(s + 1) << bits) / ns) - x.lo : 0;
+  return x;
 }
 
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
@@ -514,36 +543,29 @@ __device__ __forceinline__ void for_tokens(const int32_t* assign, int n, F f) {
   }
 }
 
-// Collects the tokens of the clusters [c_beg, c_beg + nc) in LDS, in no fixed
-// order, and returns how many there are (only the first kSliceCap are kept);
-// `before`, if given, is this thread's count of keys of earlier clusters.  One
-// pass over the assignments, 16 loads in flight per thread: a wave
-// reserves places for all its hits of a step at once, and each thread
-// walks the bits of its own hits (an LDS counter update per key, waited for,
-// had taken 15 us per pass over 65536 keys, bound by instruction issue).
-// Ends with a barrier; *s_total is 0 before.
-__device__ __forceinline__ int collect_slice(const int32_t* assign, int n, int c_beg, int nc, int32_t* s_tok, int* s_total,
-                                             int* before = nullptr) {
+// Collects the tokens of a slice's clusters in LDS, in no fixed order, and returns
+// how many there are (only the first kSliceCap are kept).  One pass over the
+// assignments, 16 loads in flight per thread: a wave reserves places for all
+// its hits of a step at once, and each thread walks the bits of its own hits
+// (an LDS counter update per key, waited for, had taken 15 us per pass over
+// 65536 keys, bound by instruction issue).  Ends with a barrier; *s_total is 0
+// before.
+__device__ __forceinline__ int collect_slice(const int32_t* assign, int n, const Slice& sc, int32_t* s_tok, int* s_total) {
   constexpr int kIn = 16;
   const int tid = threadIdx.x, lane = tid & 63;
-  int nb = 0;
-  int c[kIn];
+  const uint32_t end = sc.end();
+  int c[kIn];  // (as loaded: what is computed here would wait here)
   auto load = [&](int64_t i0) {
 #pragma unroll
-    for (int k = 0; k < kIn; ++k) {
-      const int64_t i = i0 + tid + 1024 * k;
-      const int x = assign[min(i, (int64_t)n - 1)];
-      c[k] = i < n ? x : 0x7fffffff;
-    }
+    for (int k = 0; k < kIn; ++k) c[k] = assign[min(i0 + tid + 1024 * k, (int64_t)n - 1)];
   };
   if (n > 0) load(0);
   for (int64_t i0 = 0; i0 < n; i0 += 1024 * kIn) {
     uint32_t bits = 0;
 #pragma unroll
-    for (int k = 0; k < kIn; ++k) {
-      if (before) nb += c[k] < c_beg ? 1 : 0;
-      bits |= (uint32_t)(c[k] - c_beg) < (uint32_t)nc ? 1u << k : 0u;
-    }
+    for (int k = 0; k < kIn; ++k) bits |= sc.place(c[k]) < end ? 1u << k : 0u;
+    const int64_t left = (n - i0 - tid + 1023) / 1024;  // this thread's tokens from i0 on
+    if (left < kIn) bits &= (1u << max(left, (int64_t)0)) - 1u;
     if (i0 + 1024 * kIn < n) load(i0 + 1024 * kIn);  // travels during the stores below
     const int mine = __popc(bits), incl = wave_incl_scan(mine);
     const int hits = __builtin_amdgcn_readlane(incl, 63);
@@ -554,12 +576,11 @@ __device__ __forceinline__ int collect_slice(const int32_t* assign, int n, int c
     for (; bits; bits &= bits - 1, ++pos)
       if (pos < kSliceCap) s_tok[pos] = (int)i0 + tid + 1024 * (__ffs((int)bits) - 1);
   }
-  if (before) *before = nb;
   __syncthreads();
   return *s_total;
 }
 
-// Exclusive scan in place of s[0..count) (count <= kSliceMax) in LDS by 1024
+// Exclusive scan in place of s[0..count) in LDS by 1024
 // threads, and the sum over them of `mine`.  Ends with a barrier.
 __device__ __forceinline__ int slice_scan(int32_t* s, int count, int mine, int* s_w) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -613,70 +634,85 @@ __device__ __forceinline__ void sort_small(const int32_t* list, int m, uint32_t*
   __builtin_amdgcn_wave_barrier();
 }
 
-// The same for any m (tokens below n): into s_w (kOrdWords words) up to
-// kRankMax members (counted ranks), else into `out` (a bitmap of the tokens,
-// window by window).
-__device__ __forceinline__ void sort_members(const int32_t* list, int m, int n, uint32_t* s_w, int32_t* out, int32_t* rank,
-                                             int lane) {
-  if (m <= 64) {
-    sort_small(list, m, s_w, rank, lane);
-  } else if (m <= kRankMax) {
-    constexpr int kE = kRankMax / 64;
-    int x[kE], r[kE];
+// The same for m <= kRankMax members, by counting in LDS.
+__device__ __forceinline__ void sort_members(const int32_t* list, int m, uint32_t* s_w, int32_t* rank, int lane) {
+  if (m <= kSmall) return sort_small(list, m, s_w, rank, lane);
+  constexpr int kE = kRankMax / 64;
+  int x[kE], r[kE];
 #pragma unroll
-    for (int e = 0; e < kE; ++e) {
-      const int i = lane + 64 * e;
-      x[e] = i < m ? list[i] : 0x7fffffff;
-      r[e] = 0;
-      s_w[kRankMax + i] = (uint32_t)x[e];
-    }
-    __builtin_amdgcn_wave_barrier();
-    for (int i = 0; i < m; i += 4) {  // (entries past m compare as larger)
-      const uint4 y = *reinterpret_cast<const uint4*>(s_w + kRankMax + i);
-#pragma unroll
-      for (int e = 0; e < kE; ++e)
-        r[e] += ((int)y.x < x[e] ? 1 : 0) + ((int)y.y < x[e] ? 1 : 0) + ((int)y.z < x[e] ? 1 : 0) + ((int)y.w < x[e] ? 1 : 0);
-    }
-#pragma unroll
-    for (int e = 0; e < kE; ++e)
-      if (lane + 64 * e < m) {
-        s_w[r[e]] = (uint32_t)x[e];
-        rank[x[e]] = r[e];
-      }
-  } else {
-    int base = 0;
-    for (int w0 = 0; w0 < n; w0 += kBitTokens) {
-      constexpr int kW = kBitTokens / 32 / 64;  // words per lane
-#pragma unroll
-      for (int k = 0; k < kW; ++k) s_w[k * 64 + lane] = 0u;
-      __builtin_amdgcn_wave_barrier();
-      for (int i = lane; i < m; i += 64) {
-        const int t = list[i] - w0;
-        if (t >= 0 && t < kBitTokens) atomicOr(&s_w[t >> 5], 1u << (t & 31));
-      }
-      __builtin_amdgcn_wave_barrier();
-      int cnt = 0;
-      for (int k = 0; k < kW; ++k) cnt += __popc(s_w[lane * kW + k]);
-      const int incl = wave_incl_scan(cnt);
-      int pos = base + incl - cnt;
-      for (int k = 0; k < kW; ++k)
-        for (uint32_t b = s_w[lane * kW + k]; b; b &= b - 1) {
-          const int t = w0 + (lane * kW + k) * 32 + __ffs((int)b) - 1;
-          out[pos] = t;
-          rank[t] = pos++;
-        }
-      base += __builtin_amdgcn_readlane(incl, 63);
-      __builtin_amdgcn_wave_barrier();
-    }
-    __threadfence_block();
+  for (int e = 0; e < kE; ++e) {
+    const int i = lane + 64 * e;
+    x[e] = i < m ? list[i] : 0x7fffffff;
+    r[e] = 0;
+    s_w[kRankMax + i] = (uint32_t)x[e];
   }
   __builtin_amdgcn_wave_barrier();
+  for (int i = 0; i < m; i += 4) {  // (entries past m compare as larger)
+    const uint4 y = *reinterpret_cast<const uint4*>(s_w + kRankMax + i);
+#pragma unroll
+    for (int e = 0; e < kE; ++e)
+      r[e] += ((int)y.x < x[e] ? 1 : 0) + ((int)y.y < x[e] ? 1 : 0) + ((int)y.z < x[e] ? 1 : 0) + ((int)y.w < x[e] ? 1 : 0);
+  }
+#pragma unroll
+  for (int e = 0; e < kE; ++e)
+    if (lane + 64 * e < m) {
+      s_w[r[e]] = (uint32_t)x[e];
+      rank[x[e]] = r[e];
+    }
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The workgroup (1024 threads) sorts a cluster's m members (tokens below n) by a
+// bitmap of the tokens in s_bits (kBitTokens / 32 words), window by window: into
+// `out`, with their ranks.  A list of 32768 of 65536 tokens: about 12 us (one wave
+// with windows of 16384 tokens 1.2 ms).  Begins and ends with a barrier.
+__device__ __forceinline__ void sort_by_bitmap(const int32_t* list, int m, int n, uint32_t* s_bits, int32_t* out, int32_t* rank,
+                                               int* s_w) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int base = 0;
+  for (int64_t w0 = 0; w0 < n; w0 += kBitTokens) {
+    const int words = (int)((min((int64_t)kBitTokens, n - w0) + 31) / 32);
+    const int kw = (words + 1023) / 1024, beg = min(words, tid * kw), end = min(words, beg + kw);  // this thread's words
+    __syncthreads();  // the window before is read
+    for (int k = tid; k < words; k += 1024) s_bits[k] = 0u;
+    __syncthreads();
+    constexpr int kIn = 8;
+    for (int64_t i0 = tid; i0 < m; i0 += 1024 * kIn) {
+      int64_t t[kIn];
+#pragma unroll
+      for (int k = 0; k < kIn; ++k) t[k] = list[min(i0 + 1024 * k, (int64_t)m - 1)] - w0;  // (the last one again past the end)
+#pragma unroll
+      for (int k = 0; k < kIn; ++k)
+        if (t[k] >= 0 && t[k] < kBitTokens && t[k] + w0 < n) atomicOr(&s_bits[t[k] >> 5], 1u << (t[k] & 31));
+    }
+    __syncthreads();
+    int cnt = 0;
+    for (int k = beg; k < end; ++k) cnt += __popc(s_bits[k]);
+    const int incl = wave_incl_scan(cnt);
+    if (lane == 63) s_w[wave] = incl;
+    __syncthreads();
+    int pos = base + incl - cnt, all = 0;
+    for (int w = 0; w < 16; ++w) {
+      pos += w < wave ? s_w[w] : 0;
+      all += s_w[w];
+    }
+    for (int k = beg; k < end; ++k)
+      for (uint32_t b = s_bits[k]; b; b &= b - 1, ++pos) {
+        const int t = (int)w0 + k * 32 + __ffs((int)b) - 1;
+        out[min(pos, m - 1)] = t;  // (pos < m: the members are distinct)
+        rank[t] = pos;
+      }
+    base += all;
+  }
+  __threadfence_block();
+  __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
 // centroid = bf16(mean of members), of the slice's clusters that gained or lost a
-// key (all of them in the first iteration).  Their members, collected in LDS
-// by one pass over the assignments, are sorted by token and summed:
+// key (all of them in the first iteration), and their sizes (into the offsets
+// array, scanned at the end).  Their members, collected in LDS by one pass over
+// the assignments, are sorted by token and summed:
 //  - a wave per cluster of up to 64 members, the next cluster's members sorted
 //    while this one's rows are in flight;
 //  - larger ones (on a mixture, a centroid between components collects the keys
@@ -684,42 +720,57 @@ __device__ __forceinline__ void sort_members(const int32_t* list, int m, int n, 
 //    interleaved chains that every sum consists of, with 32 rows of a chain
 //    in flight (16 rows at a time in one wave, the largest cluster had set the
 //    kernel's time).
-// 65536 x 8 keys: 116 us in the first iteration (the gather of every key), 21 to
-// 36 later, against 134 and 35 to 55 with a wave for every cluster.
-// A slice of more than kSliceCap keys (few clusters) takes two passes and lists
-// in memory, a wave per cluster.
+// 65536 x 8 keys of a mixture: 73 us in the first iteration (the gather of every
+// key), 48 to 21 later.
+// A slice of more than kSliceCap keys (a cluster of thousands, or fewer clusters
+// than slices) takes two passes and lists in memory: there a wave takes
+// clusters of up to kRankMax members, the workgroup sorts each larger one by a
+// bitmap, and the four chains' waves sum it.  A wave for each of them (windows of
+// 16384 tokens, 16 rows in flight) had made one iteration slower than counting
+// tiles and a wave per mean: 65536 x 8 keys of which half are zero, ten iterations
+// 37.1 ms, now 12.5 (25.3 by tiles); 131072 x 8 keys, one iteration, 1 / 16 / 256 clusters
+// 12.5 / 4.7 / 1.14 ms, now 3.0 / 1.1 / 0.73 (7.6 / 2.7 / 0.73); 81 distinct keys among 65536, two
+// iterations 1.20 ms, now 0.66 (1.04).
 // grid (slices, BG), 1024 threads; per: clusters per slice
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
-  extern __shared__ __align__(16) int32_t s_dyn[];  // [per] starts, [per] sizes, [per] dirty / place among the changed
+  // [2 per] starts, [2 per] sizes, [2 per] dirty / place among the changed, [2 per] 16-bit list of the clusters of one wave each
+  extern __shared__ __align__(16) int32_t s_dyn[];
   __shared__ __align__(16) uint32_t s_ord[16][kOrdWords];
   __shared__ int32_t s_tok[kSliceCap], s_mem[kSliceCap];
-  __shared__ int s_big[kSliceCap / kSmall];
-  __shared__ int s_w[32], s_n, s_base, s_total, s_nbig;
+  __shared__ int s_big_lds[kSliceCap / kSmall];
+  __shared__ int s_w[32], s_n, s_base, s_total, s_nbig, s_nsmall;
+  static_assert(2 * kSliceMax <= kSliceCap, "the collected tokens' place holds a list of a slice's clusters");
   const int p = blockIdx.y;
   if (*done_flag(a, p)) return;
   const Problem q = problem(a, p);
-  const int c_beg = blockIdx.x * per, nc = min(per, q.C - c_beg);
+  const Slice sc = make_slice(q.C, per, blockIdx.x);
+  const int nc = sc.nr;
   if (nc <= 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sl = lane & 15, grp = lane >> 4;
-  int32_t *s_beg = s_dyn, *s_cnt = s_dyn + per, *s_slot = s_dyn + 2 * per;
+  int32_t *s_beg = s_dyn, *s_cnt = s_dyn + 2 * per, *s_slot = s_dyn + 4 * per;
+  uint16_t* s_small = reinterpret_cast<uint16_t*>(s_dyn + 6 * per);
   int any = 0;
   for (int c = tid; c < nc; c += 1024) {
-    const int64_t at = q.cl_base + c_beg + c;
-    const int d = a.iter == 1 ? 1 : a.dirty[at];
+    int d = 0;
+    if (sc.id(c) < q.C) {
+      const int64_t at = q.cl_base + sc.id(c);
+      d = a.iter == 1 ? 1 : a.dirty[at];
+      a.dirty[at] = 0;
+      a.moved[at] = 0;
+    }
     any |= d;
     s_beg[c] = 0;
     s_slot[c] = d;
-    a.dirty[at] = 0;
-    a.moved[at] = 0;
   }
-  if (tid == 0) s_n = s_total = s_nbig = 0;
+  if (tid == 0) s_n = s_total = s_nbig = s_nsmall = 0;
   if (!__syncthreads_or(any)) return;
   const int32_t* assign = a.assign + q.tok_base;
   int32_t* rank = a.rank + q.tok_base;
-  int before = 0;  // keys of the clusters before the slice (used by the lists in memory)
-  const int total = collect_slice(assign, q.n, c_beg, nc, s_tok, &s_total);
+  const int total = collect_slice(assign, q.n, sc, s_tok, &s_total);
   const bool in_lds = total <= kSliceCap;
+  const uint32_t end = sc.end();
+  int before = 0;  // keys of the slices before this one (the place of its lists in memory)
   constexpr int kE = kSliceCap / 1024;
   int tok_e[kE], cl_e[kE], place[kE];
   if (in_lds) {
@@ -729,27 +780,35 @@ __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
       place[e] = -1;
     }
 #pragma unroll
-    for (int e = 0; e < kE; ++e) cl_e[e] = tid + 1024 * e < total ? assign[tok_e[e]] - c_beg : -1;
+    for (int e = 0; e < kE; ++e) cl_e[e] = tid + 1024 * e < total ? sc.local(sc.place(assign[tok_e[e]])) : -1;
 #pragma unroll
     for (int e = 0; e < kE; ++e)
       if (cl_e[e] >= 0 && s_slot[cl_e[e]]) place[e] = atomicAdd(&s_beg[cl_e[e]], 1);
   } else {
     for_tokens(assign, q.n, [&](int, int c) {
-      before += c < c_beg ? 1 : 0;
-      const uint32_t k = (uint32_t)(c - c_beg);
-      if (k < (uint32_t)nc && s_slot[k]) atomicAdd(&s_beg[k], 1);
+      const uint32_t x = sc.place(c);
+      before += __brev((uint32_t)c) < (uint32_t)sc.lo << sc.shift ? 1 : 0;
+      if (x < end && s_slot[sc.local(x)]) atomicAdd(&s_beg[sc.local(x)], 1);
     });
   }
   __syncthreads();
+  // the clusters to take (a slice may hold many empty or unchanged ones, and numbers that
+  // no cluster has): those of more than `large` members, four waves each, and
+  // the others (with lists in memory the former in the collected tokens' place)
+  const int large = in_lds ? kSmall : kRankMax;
+  int* s_big = in_lds ? s_big_lds : s_tok;
   for (int c = tid; c < nc; c += 1024) {
     const int m = s_beg[c];
     s_cnt[c] = m;
+    if (s_slot[c]) a.offsets[q.off_base + sc.id(c)] = m;
     if (m == 0) s_slot[c] = -1;  // nothing to do: an empty cluster keeps its centroid
-    else if (in_lds && m > kSmall) s_big[atomicAdd(&s_nbig, 1)] = c;
+    else if (m > large) s_big[atomicAdd(&s_nbig, 1)] = c;
+    else s_small[atomicAdd(&s_nsmall, 1)] = (uint16_t)c;
   }
   __syncthreads();
   before = slice_scan(s_beg, nc, before, s_w);
   int32_t* members = a.members + q.tok_base + before;
+  int32_t* sorted = a.perm + q.tok_base + before;  // (perm: scratch until the layout)
   if (in_lds) {
 #pragma unroll
     for (int e = 0; e < kE; ++e)
@@ -757,8 +816,8 @@ __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
   } else {
     const int room = q.n - before;  // (the lists of the slices' clusters fit: they are disjoint)
     for_tokens(assign, q.n, [&](int t, int c) {
-      const uint32_t k = (uint32_t)(c - c_beg);
-      if (k < (uint32_t)nc && s_cnt[k] > 0) members[min(atomicAdd(&s_beg[k], 1), room - 1)] = t;
+      const uint32_t x = sc.place(c);
+      if (x < end && s_cnt[sc.local(x)] > 0) members[min(atomicAdd(&s_beg[sc.local(x)], 1), room - 1)] = t;
     });
     __syncthreads();
     for (int c = tid; c < nc; c += 1024) s_beg[c] -= s_cnt[c];  // the cursors ended at the lists' ends
@@ -769,7 +828,7 @@ __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
   // cluster c of m members with the sums s of its lane's 8 dimensions (the same
   // in the four lane-groups): store the centroid if it changed
   auto finish = [&](int c, int m, const float (&s)[8], const uint4& old) {
-    const int64_t at = q.cl_base + c_beg + c;
+    const int64_t at = q.cl_base + sc.id(c);
     const float inv = 1.f / (float)m;
     float cn = 0.f;
     uint32_t out[4];
@@ -794,15 +853,19 @@ __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
     }
   };
 
-  // ---- clusters of more than kSmall members
+  // ---- clusters of more than `large` members
   const int nbig = __builtin_amdgcn_readfirstlane(s_nbig);
   if (nbig > 0) {
-    // their members by token into s_tok: a wave ranks 64 members of a cluster
-    // against all of its members
+    // their members by token, into s_tok (a wave ranks 64 members of a cluster
+    // against all of its members) or, from the lists in memory, into `sorted`
     int task = 0;
     for (int i = 0; i < nbig; ++i) {
       const int c = __builtin_amdgcn_readfirstlane(s_big[i]);
       const int b0 = __builtin_amdgcn_readfirstlane(s_beg[c]), m = __builtin_amdgcn_readfirstlane(s_cnt[c]);
+      if (!in_lds) {
+        sort_by_bitmap(members + b0, m, q.n, &s_ord[0][0], sorted + b0, rank, s_w);
+        continue;
+      }
       for (int j0 = 0; j0 < m; j0 += 64, ++task) {
         if ((task & 15) != wave) continue;
         const int x = j0 + lane < m ? s_mem[b0 + j0 + lane] : 0x7fffffff;
@@ -825,13 +888,19 @@ __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
       const int c = __builtin_amdgcn_readfirstlane(on ? s_big[i0 + quad] : 0);
       const int b0 = __builtin_amdgcn_readfirstlane(s_beg[c]), m = on ? __builtin_amdgcn_readfirstlane(s_cnt[c]) : 0;
       uint4 old = make_uint4(0, 0, 0, 0);
-      if (on && chain == 0) old = *reinterpret_cast<const uint4*>(a.centroids + (q.cl_base + c_beg + c) * kHeadDim + sl * 8);
+      if (on && chain == 0) old = *reinterpret_cast<const uint4*>(a.centroids + (q.cl_base + sc.id(c)) * kHeadDim + sl * 8);
       // the chain's rows chain, chain + 4, ...; this lane's two dimensions
       float s0 = 0.f, s1 = 0.f;
       const uint32_t* Kl = reinterpret_cast<const uint32_t*>(a.K + q.tok_base * kHeadDim) + lane;
       const int nr = (m - chain + 3) / 4;
+      auto row = [&](int r) {  // (r < nr, or the last row again)
+        const int i = b0 + min(chain + 4 * r, m - 1);
+        return in_lds ? s_tok[i] : sorted[i];
+      };
+      int t_next = nr > 0 ? row(lane) : 0;
       for (int r0 = 0; r0 < nr; r0 += 64) {
-        const int t = s_tok[b0 + min(chain + 4 * (r0 + lane), m - 1)];
+        const int t = t_next;
+        if (r0 + 64 < nr) t_next = row(r0 + 64 + lane);  // travels during the sums
         const int rm = min(64, nr - r0);
 #pragma unroll
         for (int k0 = 0; k0 < 64; k0 += 32) {
@@ -863,46 +932,35 @@ __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
   }
 
   // ---- the others: a wave per cluster
-  auto next = [&](int c) {  // this wave's clusters, from c on
-    while (c < nc && (s_cnt[c] == 0 || (in_lds && s_cnt[c] > kSmall))) c += 16;
-    return __builtin_amdgcn_readfirstlane(c);
-  };
   constexpr int kHalf = kOrdWords / 2;  // (two buffers of up to kSmall members, or one of the lists in memory)
   auto sort = [&](int c, int buf) {
     const int b0 = __builtin_amdgcn_readfirstlane(s_beg[c]), m = __builtin_amdgcn_readfirstlane(s_cnt[c]);
     if (in_lds) sort_small(s_mem + b0, m, s_ord[wave] + buf * kHalf, rank, lane);
-    else sort_members(members + b0, m, q.n, s_ord[wave], a.perm + q.tok_base + before + b0, rank, lane);  // (perm: scratch)
+    else sort_members(members + b0, m, s_ord[wave], rank, lane);
   };
-  int c = next(wave);
-  if (c < nc && in_lds) sort(c, 0);
-  for (int buf = 0; c < nc; buf ^= 1) {
-    const int b0 = __builtin_amdgcn_readfirstlane(s_beg[c]), m = __builtin_amdgcn_readfirstlane(s_cnt[c]);
-    const uint4 old = *reinterpret_cast<const uint4*>(a.centroids + (q.cl_base + c_beg + c) * kHeadDim + sl * 8);
+  const int nsmall = __builtin_amdgcn_readfirstlane(s_nsmall);
+  auto small = [&](int i) { return __builtin_amdgcn_readfirstlane((int)s_small[min(i, nsmall - 1)]); };
+  if (wave < nsmall && in_lds) sort(small(wave), 0);
+  for (int i = wave, buf = 0; i < nsmall; i += 16, buf ^= 1) {
+    const int c = small(i);
+    const int m = __builtin_amdgcn_readfirstlane(s_cnt[c]);
+    const uint4 old = *reinterpret_cast<const uint4*>(a.centroids + (q.cl_base + sc.id(c)) * kHeadDim + sl * 8);
     if (!in_lds) sort(c, 0);
     const uint32_t* ord = s_ord[wave] + (in_lds ? buf * kHalf : 0);
-    const int32_t* sorted = a.perm + q.tok_base + before + b0;
     // lane-group grp sums members grp, grp + 4, grp + 8, ... in that order;
     // 16 rows per step, their key rows loaded together
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     uint4 v[4];
     auto load = [&](int r0) {
       int tok[4];
-      if (in_lds || m <= kRankMax) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) tok[k] = (int)ord[min(r0 + grp + 4 * k, m - 1)];
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) tok[k] = sorted[min(r0 + grp + 4 * k, m - 1)];
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) tok[k] = min(max(tok[k], 0), q.n - 1);
+      for (int k = 0; k < 4; ++k) tok[k] = min(max((int)ord[min(r0 + grp + 4 * k, m - 1)], 0), q.n - 1);
 #pragma unroll
       for (int k = 0; k < 4; ++k)
         v[k] = *reinterpret_cast<const uint4*>(a.K + (q.tok_base + tok[k]) * kHeadDim + sl * 8);
     };
     load(0);
-    const int c_next = next(c + 16);
-    if (c_next < nc && in_lds) sort(c_next, buf ^ 1);
+    if (i + 16 < nsmall && in_lds) sort(small(i + 16), buf ^ 1);
     for (int r0 = 0; r0 < m; r0 += 16) {
       if (r0 > 0) load(r0);
 #pragma unroll
@@ -922,7 +980,6 @@ __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
       s[e] += __shfl_xor(s[e], 32, 64);
     }
     finish(c, m, s, old);
-    c = c_next;
   }
   // the changed centroids join the problem's list (its order does not matter:
   // equal scores among them list the key); the rows written above are read back
@@ -933,87 +990,76 @@ __global__ __launch_bounds__(1024) void km_update_kernel(KmArgs a, int per) {
   __syncthreads();
   for (int j = tid >> 4; j < nc; j += 64) {
     if (s_slot[j] < 0) continue;
-    const int64_t at = q.cl_base + c_beg + j, to = q.cl_base + s_base + s_slot[j];
+    const int64_t at = q.cl_base + sc.id(j), to = q.cl_base + s_base + s_slot[j];
     *reinterpret_cast<uint4*>(a.d_rows + to * kHeadDim + sl * 8) =
         *reinterpret_cast<const uint4*>(a.centroids + at * kHeadDim + sl * 8);
     if (sl == 0) {
       a.d_norm[to] = a.cnorm[at];
-      a.d_id[to] = c_beg + j;
+      a.d_id[to] = sc.id(j);
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// the layout: offsets of the slice's clusters and perm of their rows (every key
-// goes to its rank among its cluster's).  grid (slices, BG), 1024 threads
+// offsets: exclusive scan of the cluster sizes, in place.  grid BG, 1024 threads
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void km_layout_kernel(KmArgs a, int per) {
-  extern __shared__ __align__(16) int32_t s_dyn[];  // [per] rows before each cluster
-  __shared__ int32_t s_tok[kSliceCap];
-  __shared__ int s_w[32], s_total;
-  const int p = blockIdx.y;
-  const Problem q = problem(a, p);
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.offsets[q.off_base + q.C] = q.n;
-  const int c_beg = blockIdx.x * per, nc = min(per, q.C - c_beg);
-  if (nc <= 0) return;
-  const int tid = threadIdx.x;
-  for (int c = tid; c < nc; c += 1024) s_dyn[c] = 0;
-  if (tid == 0) s_total = 0;
-  __syncthreads();
-  const int32_t* assign = a.assign + q.tok_base;
-  const int32_t* rank = a.rank + q.tok_base;
-  int32_t* perm = a.perm + q.tok_base;
-  int before = 0;
-  const int total = collect_slice(assign, q.n, c_beg, nc, s_tok, &s_total, &before);
-  const bool in_lds = total <= kSliceCap;
-  constexpr int kE = kSliceCap / 1024;
-  int tok_e[kE], cl_e[kE], rk[kE];
-  if (in_lds) {
+__global__ __launch_bounds__(1024) void km_layout_kernel(KmArgs a) {
+  __shared__ int s_w[16];
+  const Problem q = problem(a, blockIdx.x);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int32_t* off = a.offsets + q.off_base;
+  constexpr int kPer = 8;
+  int carry = 0;
+  for (int64_t c0 = 0; c0 < q.C; c0 += 1024 * kPer) {
+    const int64_t c = c0 + tid * kPer;
+    int v[kPer], loc = 0;
 #pragma unroll
-    for (int e = 0; e < kE; ++e) tok_e[e] = s_tok[max(min(tid + 1024 * e, total - 1), 0)];  // (unused when total is 0)
+    for (int e = 0; e < kPer; ++e) v[e] = c + e < q.C ? off[c + e] : 0;
 #pragma unroll
-    for (int e = 0; e < kE; ++e) {
-      const bool in = tid + 1024 * e < total;
-      cl_e[e] = in ? assign[tok_e[e]] - c_beg : -1;
-      rk[e] = in ? rank[tok_e[e]] : 0;
+    for (int e = 0; e < kPer; ++e) loc += v[e];
+    const int incl = wave_incl_scan(loc);  // DPP, no LDS
+    if (lane == 63) s_w[wave] = incl;
+    __syncthreads();
+    int run = carry + incl - loc;
+    for (int w = 0; w < 16; ++w) {
+      run += w < wave ? s_w[w] : 0;
+      carry += s_w[w];
     }
 #pragma unroll
-    for (int e = 0; e < kE; ++e)
-      if (cl_e[e] >= 0) atomicAdd(&s_dyn[cl_e[e]], 1);
-  } else {
-    for_tokens(assign, q.n, [&](int, int c) {
-      const uint32_t k = (uint32_t)(c - c_beg);
-      if (k < (uint32_t)nc) atomicAdd(&s_dyn[k], 1);
-    });
+    for (int e = 0; e < kPer; ++e) {
+      if (c + e < q.C) off[c + e] = run;
+      run += v[e];
+    }
+    __syncthreads();  // s_w is rewritten
   }
-  __syncthreads();
-  before = slice_scan(s_dyn, nc, before, s_w);
-  for (int c = tid; c < nc; c += 1024) a.offsets[q.off_base + c_beg + c] = before + s_dyn[c];
-  if (in_lds) {
-#pragma unroll
-    for (int e = 0; e < kE; ++e)
-      if (cl_e[e] >= 0) perm[min(max(before + s_dyn[cl_e[e]] + rk[e], 0), q.n - 1)] = tok_e[e];
-  } else {
-    for_tokens(assign, q.n, [&](int t, int c) {
-      const uint32_t k = (uint32_t)(c - c_beg);
-      if (k < (uint32_t)nc) perm[min(max(before + s_dyn[k] + rank[t], 0), q.n - 1)] = t;
-    });
-  }
+  if (tid == 0) off[q.C] = q.n;
 }
 
 // ---------------------------------------------------------------------------
-// K_sorted[row] = K[perm[row]] (and V).  grid (ceil(nmax/16), BG), 256 threads
+// the cluster order: every token's row is its cluster's first row plus its rank;
+// perm[row] = token, K_sorted[row] = K[token] (and V).  Bound by memory: the rows
+// are read in token order and written to their places (past the caches: 1% of a
+// call of two iterations).  131072 x 2 sequences x 8 heads: with the scan of the sizes 390 us;
+// placing the tokens by a pass over the assignments in every slice of the
+// clusters, then gathering the rows, had taken 105 + 348.
+// grid (ceil(nmax/16), BG), 256 threads
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void km_permute_kv_kernel(KmArgs a) {
+__global__ __launch_bounds__(256) void km_permute_kernel(KmArgs a) {
   const int p = blockIdx.y;
   const Problem q = problem(a, p);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sl = lane & 15, grp = lane >> 4;
-  const int r = blockIdx.x * 16 + wave * 4 + grp;
-  if (r >= q.n) return;
-  const int tok = min(max(a.perm[q.tok_base + r], 0), q.n - 1);
-  const int64_t src = (q.tok_base + tok) * kHeadDim + sl * 8, dst = (q.tok_base + r) * kHeadDim + sl * 8;
-  if (a.K_sorted) *reinterpret_cast<uint4*>(a.K_sorted + dst) = load_stream16(a.K + src);
-  if (a.V_sorted) *reinterpret_cast<uint4*>(a.V_sorted + dst) = load_stream16(a.V + src);
+  const int t = blockIdx.x * 16 + wave * 4 + grp;
+  if (t >= q.n) return;
+  const int64_t src = (q.tok_base + t) * kHeadDim + sl * 8;
+  uint4 k = make_uint4(0, 0, 0, 0), v = k;
+  if (a.K_sorted) k = load_stream16(a.K + src);
+  if (a.V_sorted) v = load_stream16(a.V + src);
+  const int c = a.assign[q.tok_base + t], rk = a.rank[q.tok_base + t];
+  const int row = min(max(a.offsets[q.off_base + max(c, 0)] + rk, 0), q.n - 1);
+  if (sl == 0) a.perm[q.tok_base + row] = t;
+  const int64_t dst = (q.tok_base + row) * kHeadDim + sl * 8;
+  if (a.K_sorted) store_stream16(a.K_sorted + dst, k);
+  if (a.V_sorted) store_stream16(a.V_sorted + dst, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -1106,11 +1152,14 @@ hipError_t run_kmeans(const uint16_t* K, const uint16_t* V, const int64_t* kv_in
   const dim3 g_cl((Cm + 3) / 4, BG), g_tok((unsigned)((nmax + kAsgTok - 1) / kAsgTok), BG);
   // slices of the clusters: at least one workgroup for each of the 256 compute
   // units and few enough keys per slice for LDS (half of kSliceCap on
-  // average), at least 16 clusters (a wave each) and at most kSliceMax
-  const int64_t ns = std::max<int64_t>((256 + BG - 1) / BG, (nmax + kSliceCap / 2 - 1) / (kSliceCap / 2));
-  const int per = (int)std::min<int64_t>(kSliceMax, std::max<int64_t>(16, (Cm + ns - 1) / ns));
+  // average); no more than the latter needs below 16 clusters (a wave each), and
+  // at most kSliceMax clusters
+  const int64_t ns_lds = std::max<int64_t>(1, (nmax + kSliceCap / 2 - 1) / (kSliceCap / 2));
+  const int64_t ns = std::max<int64_t>((256 + BG - 1) / BG, ns_lds);
+  const int64_t least = std::min<int64_t>(16, (Cm + ns_lds - 1) / ns_lds);
+  const int per = (int)std::min<int64_t>(kSliceMax, std::max<int64_t>(least, (Cm + ns - 1) / ns));
   const dim3 g_slice((Cm + per - 1) / per, BG);
-  const size_t lds_upd = (size_t)per * 12, lds_lay = (size_t)per * 4;
+  const size_t lds_upd = (size_t)per * 28;
   // listed keys: work items in flight per problem, three workgroups on each of
   // the 256 compute units together, at most as many as a problem has items
   const int64_t items = (int64_t)g_tok.x * ((Cm + kListCen - 1) / kListCen);
@@ -1132,12 +1181,9 @@ hipError_t run_kmeans(const uint16_t* K, const uint16_t* V, const int64_t* kv_in
     e = hipGetLastError();
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(km_layout_kernel, g_slice, dim3(1024), lds_lay, st, a, per);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess && (K_sorted || V_sorted)) {
     if (!V) a.V_sorted = nullptr;
-    hipLaunchKernelGGL(km_permute_kv_kernel, dim3((unsigned)((nmax + 15) / 16), BG), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(km_layout_kernel, dim3(BG), dim3(1024), 0, st, a);
+    hipLaunchKernelGGL(km_permute_kernel, dim3((unsigned)((nmax + 15) / 16), BG), dim3(256), 0, st, a);
     e = hipGetLastError();
   }
   return e;
