@@ -62,16 +62,12 @@ def test_kmeans_later_iterations_equal_full_steps(lens, ncl, kind, warm):
         prev = step.clusters
 
 
-@pytest.mark.parametrize("n,C", [(700, 3), (5001, 300), (20011, 4), (20011, 200), (70000, 2), (270001, 5)])
-@pytest.mark.parametrize("kind", ["mixture", "zeros"])
-def test_kmeans_one_step_layout_and_means(n, C, kind):
-    """One iteration: the layout is the stable order of the assignment, bit for bit, and every mean is that of the
+def _check_one_step(K, init):
+    """The layout is the stable order of the assignment, bit for bit, and every mean is that of the
     cluster's keys, summed in four interleaved chains (a bound of the fp32 sums: members / 4 + 2 additions, each
     2^-24 of the sum of magnitudes, then a factor and a rounding to bf16, 2^-8 with a margin of 2^-20)."""
     T = _T()
-    K = _keys(1, n, kind, n + C)
-    rng = np.random.default_rng(n)
-    init = torch.as_tensor(rng.choice(n, C, replace=False).astype(np.int32)[None], device="cuda")
+    n, C = K.shape[1], init.shape[1]
     r = T.ClusterBuilder(T.RaggedBatch([n], 1, 1), [C], max_iters=1)(K, K, init)
     a = r.assign[0].long()
     assert torch.equal(r.perm[0].long(), torch.sort(a, stable=True).indices)
@@ -86,6 +82,30 @@ def test_kmeans_one_step_layout_and_means(n, C, kind):
     got = r.clusters.centroids[0][full].double()
     assert torch.all((got - mean).abs() <= err + (mean.abs() + err) * (2.0 ** -8 + 2.0 ** -20))
     assert torch.equal(r.clusters.centroids[0][~full], K[0][init[0].long()][~full])
+    return cnt
+
+
+@pytest.mark.parametrize("C", [1, 2, 3, 64, 65, 100])
+def test_kmeans_sizes_at_the_limits_of_the_sums(C):
+    """Clusters of given sizes around the limits of a wave (64), of lists in memory (256) and of a slice's keys in
+    LDS (4096 together), in every slice; numbers of clusters at and beside powers of two."""
+    sizes = np.resize([5000, 64, 257, 1, 65, 256, 63, 1500, 4096, 300, 2, 255, 700], C)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(C)
+    lab = torch.repeat_interleave(torch.arange(C, device="cuda"), torch.as_tensor(sizes, device="cuda"))
+    lab = lab[torch.randperm(len(lab), generator=g, device="cuda")]
+    centre = torch.randn(C, 128, generator=g, device="cuda")
+    K = (centre[lab] + 0.05 * torch.randn(len(lab), 128, generator=g, device="cuda")).to(torch.bfloat16)[None]
+    first = torch.as_tensor([int((lab == c).nonzero()[0]) for c in range(C)], dtype=torch.int32, device="cuda")
+    assert np.array_equal(_check_one_step(K, first[None]).cpu().numpy(), sizes)
+
+
+@pytest.mark.parametrize("n,C", [(700, 3), (5001, 300), (20011, 4), (20011, 200), (70000, 2), (270001, 5)])
+@pytest.mark.parametrize("kind", ["mixture", "zeros"])
+def test_kmeans_one_step_layout_and_means(n, C, kind):
+    rng = np.random.default_rng(n)
+    init = torch.as_tensor(rng.choice(n, C, replace=False).astype(np.int32)[None], device="cuda")
+    _check_one_step(_keys(1, n, kind, n + C), init)
 
 
 def _cluster_set(cen, ncl):
