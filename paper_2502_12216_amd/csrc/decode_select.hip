@@ -169,13 +169,16 @@ __device__ __forceinline__ uint32_t sum_of_waves(const uint32_t* s) {
 // and whether all C of them are equal, from each thread's sums over its
 // scores of d = s - pivot (the first score: the sums then carry the spread
 // whatever the scores' common offset): sm = sum d, sq = sum d^2, nf = scores
-// that are not NaN, diff = some d is not 0.  1024 threads, one barrier.
-__device__ __forceinline__ void score_moments(float pivot, float sm, float sq, int nf, bool diff, int C, float (*s_red)[4],
+// that are not NaN, far = largest |d| (NaN, of equal infinities, left out).  Where
+// the squares leave fp32 (differences below 1e-22 or above 1e19) the scale is 1 /
+// far: with 1 or 0 all scores would share two buckets, and ranking 8192 of them
+// within a bucket takes 1.1 ms.  1024 threads, one barrier (there two more).
+__device__ __forceinline__ void score_moments(float pivot, float sm, float sq, int nf, float far, int C, float (*s_red)[4],
                                               float* mu, float* inv_sd, bool* all_equal) {
   const int wave = threadIdx.x / kWave;
   sm = wave_allsum_f(sm);  // DPP, no LDS
   sq = wave_allsum_f(sq);
-  const bool any = __any(diff);
+  const bool any = __any(far > 0.f);
   if ((threadIdx.x & (kWave - 1)) == 0)
     *reinterpret_cast<float4*>(s_red[wave]) = make_float4(sm, sq, (float)nf, any ? 1.f : 0.f);
   __syncthreads();
@@ -188,7 +191,16 @@ __device__ __forceinline__ void score_moments(float pivot, float sm, float sq, i
   const float inv_n = 1.f / fmaxf(n, 1.f), m = sm * inv_n;
   const float var = fmaxf(sq * inv_n - m * m, 0.f);
   *mu = pivot + m;
-  *inv_sd = var > 0.f ? 1.f / sqrtf(var) : 1.f;
+  if (var > 0.f && var < INFINITY) {  // (the same in all threads)
+    *inv_sd = 1.f / sqrtf(var);
+  } else {
+    far = wave_allmax_f(far);
+    __syncthreads();  // the sums are read
+    if ((threadIdx.x & (kWave - 1)) == 0) s_red[wave][0] = far;
+    __syncthreads();
+    far = wave_allmax_f(s_red[threadIdx.x & 15][0]);
+    *inv_sd = far < INFINITY ? 1.f / fmaxf(far, 0x1p-126f) : 1.f;
+  }
 }
 
 // A thread's kPer consecutive entries of an LDS array (from entry tid kPer),
@@ -393,16 +405,17 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
     }
     float sm = 0.f, sq = 0.f, mu, inv_sd;
     int nf = 0;  // of the wave
-    bool diff = false, all_equal;
+    float far = 0.f;
+    bool all_equal;
 #pragma unroll
     for (int e = 0; e < kE; ++e) {
       const float d = v[e] == v[e] ? v[e] - pivot : 0.f;
       sm += d;
       sq = fmaf(d, d, sq);
-      diff |= d != 0.f;
+      far = fmaxf(far, fabsf(d));
       nf += (int)__popcll(__ballot(v[e] == v[e]));
     }
-    score_moments(pivot, sm, sq, nf, diff, C, s_red, &mu, &inv_sd, &all_equal);
+    score_moments(pivot, sm, sq, nf, far, C, s_red, &mu, &inv_sd, &all_equal);
     if (all_equal) {
       // all scores equal: the order is the cluster id
 #pragma unroll
@@ -645,18 +658,19 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
       if (tid == 0) s_any_n = 0;
       float sm = 0.f, sq = 0.f, mu, inv_sd;
       int nf = 0;  // of the wave
-      bool diff = false, all_equal;  // (all equal: the general path orders them by id)
+      float far = 0.f;
+      bool all_equal;  // (all equal: the general path orders them by id)
 #pragma unroll
       for (int e = 0; e < kP; ++e) {
         const bool num = valid(e) && v[e] == v[e];
         const float d = num ? v[e] - pivot : 0.f;
         sm += d;
         sq = fmaf(d, d, sq);
-        diff |= d != 0.f;
+        far = fmaxf(far, fabsf(d));
         nf += (int)__popcll(__ballot(num));
       }
       // (its barrier also orders the count clears before the counting below)
-      score_moments(pivot, sm, sq, nf, diff, C, s_red, &mu, &inv_sd, &all_equal);
+      score_moments(pivot, sm, sq, nf, far, C, s_red, &mu, &inv_sd, &all_equal);
       if (!all_equal) {
         // counting (adding 0 past C, so that no branch parts the 32 updates);
         // each cluster keeps its bucket

@@ -220,6 +220,71 @@ def test_sort_cluster_sizes_beyond_the_packed_word(C, big):
     _check_selection(_decode(lens, ncl, 2, 1, 9, sizes=sizes), lens, ncl, 2, 1)
 
 
+def _scored(scores, hq=4):
+    """A decode whose cluster scores are the given ones (a centroid is its score's bf16 pair of factors in one
+    dimension): scores = (q value, centroid values [C])."""
+    T = _T()
+    qv, cv = scores
+    C = len(cv)
+    n = 2 * C
+    g = torch.Generator(device="cuda")
+    g.manual_seed(C)
+    K = torch.randn(1, n, 128, generator=g, device="cuda").to(torch.bfloat16)
+    cen = torch.zeros(1, C, 128, dtype=torch.bfloat16, device="cuda")
+    cen[0, :, 5] = cv.cuda().to(torch.bfloat16)
+    q = torch.zeros(1, hq, 128, dtype=torch.bfloat16, device="cuda")
+    q[0, :, 5] = qv
+    off = torch.arange(0, n + 1, 2, dtype=torch.int32, device="cuda")[None]
+    dec = T.SparseDecoder(T.RaggedBatch([n], hq, 1), [C], T.decode_params(0.9))
+    return dec, q, K, T.ClusterSet(cen, off.contiguous(), [C])
+
+
+def _kinds(kind, C):
+    g = torch.Generator().manual_seed(C)
+    x = torch.randn(C, generator=g)
+    if kind == "ordinary":
+        return 1.0, x
+    if kind == "tiny":  # squares of the differences underflow
+        return 1e-25, x
+    if kind == "denormal":
+        return 1e-38, x * 0.01
+    if kind == "huge":  # squares overflow, differences from the mean too
+        return 1.0, torch.where(x > 0, 1.0, -1.0) * 3.2e38 * torch.rand(C, generator=g).clamp_min(0.1) * (x.abs() < 0.002)
+    if kind == "infinite":
+        return 1.0, torch.full((C,), float("inf"))
+    return 1.0, torch.where(x > 0, float("inf"), x)  # some infinite
+
+
+@pytest.mark.parametrize("C", [200, 3000, 8192, 16384, 20001, 33000])
+@pytest.mark.parametrize("kind", ["tiny", "denormal", "huge", "infinite", "some infinite"])
+def test_sort_of_extreme_scores(C, kind):
+    dec, q, K, cl = _scored(_kinds(kind, C))
+    dec(q, K, K, cl)
+    v = {k: t.cpu().numpy() for k, t in dec.view().items()}
+    for h in range(4):
+        order = np.lexsort((np.arange(C), -v["scores"][0, h, :C]))
+        assert np.array_equal(v["order"][0, h, :C], order), h
+
+
+def test_sort_time_of_tiny_or_equal_infinite_scores():
+    """8192 clusters whose scores' squares underflow, or which are all infinite: the buckets of the sort must not
+    crowd (quadratic work: 40 times an ordinary call).  A bound of three ordinary calls."""
+    def us(kind):
+        dec, q, K, cl = _scored(_kinds(kind, 8192))
+        best = float("inf")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            dec(q, K, K, cl)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3)
+        return best
+    t = {k: us(k) for k in ("ordinary", "tiny", "infinite")}
+    print({k: round(x, 1) for k, x in t.items()})
+    assert t["tiny"] <= 3 * t["ordinary"] and t["infinite"] <= 3 * t["ordinary"], t
+
+
 @pytest.mark.parametrize("C", [6143, 6144, 6145, 13000])
 @pytest.mark.parametrize("target", [0.3, 0.97])
 def test_union_of_eight_heads(C, target):
