@@ -540,8 +540,8 @@ static tactic_status dense_decode_impl(const uint16_t* q, const uint16_t* K, con
   const size_t need = dense_workspace_bytes(shape, tactic::kMaxAttnGrid);
   if (!workspace || workspace_bytes < need)
     return fail(TACTIC_ERR_WORKSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, need);
-  int resident = 0;
-  hipError_t e = tactic::attn_resident_grid(G, (int)BG, pk != nullptr, &resident);
+  int resident = 0, cus = 1;
+  hipError_t e = tactic::attn_resident_grid(G, (int)BG, pk != nullptr, &resident, &cus);
   if (e != hipSuccess) return hip_fail(e, "attention occupancy query");
   resident = std::min(resident, tactic::kMaxAttnGrid);
   tactic::AttnArgs aa{};
@@ -555,6 +555,7 @@ static tactic_status dense_decode_impl(const uint16_t* q, const uint16_t* K, con
   aa.Hq = shape->n_q_heads;
   aa.Hkv = shape->n_kv_heads;
   aa.dense = 1;
+  aa.cus = cus;
   aa.NV = shape->n_kv_heads;
   aa.kv_div = 1;
   aa.total = shape->total_tokens;

@@ -41,18 +41,30 @@ __device__ __forceinline__ int64_t group_tokens(const AttnArgs& a, int bg) {
 // takes a small call as long as its first (2% of 32768 tokens, 8 groups,
 // attention: 14.4 us at 256 / 96 units, 11.7 at 64 / 32, 8.4 at 64 / 128 to
 // 256; 1M tokens 19.1 -> 17.1, 4 x 131072 at 25%: 87.4 -> 85.8 to 87.2).  Shares
-// below 64 units gain nothing and give the combine more partials.  A dense
-// share has no range lookup to spread: at least 256 units (13193 tokens, 8 KV
-// heads, with the combine: 19.8 us; 21.5 at 64, 22.7 at 192, 21.1 at 320).
-struct Split {
-  int64_t segment_cost, min_share;
-};
-__device__ __forceinline__ Split split_rule(const AttnArgs& a) {
-  return Split{192, a.dense ? 256 : 64};
+// below 64 units gain nothing and give the combine more partials.
+constexpr int64_t kSegmentCost = 192;
+constexpr int64_t kSparseShare = 64;
+// A dense share has no range lookup to spread: 256 units, and where that makes
+// only a few shares more than a whole number per compute unit, that whole number
+// of larger ones, since otherwise some compute units take one share more than the
+// others; up to one per compute unit, at least 192 units.  Dense decodes of 1, 2, 4 and 8
+// sequences of 1024 to 65536 tokens (twenty lengths; 1, 4 and 8 heads per KV head,
+// contiguous and paged; caches cold), rounded against shares of 256: 0.85 to 0.92 of the
+// time between 1 and 1.25 or 2 and 2.25 shares per compute unit (8192 tokens x 2 sequences x 8
+// KV heads, 524 shares: 27.1 us, 512: 23.0), 0.95 to 0.99 at 1.44, 1.03 at 1.5 to 1.8 (two
+// shares of less than 256 for each); 0.95 below 0.7; from 3 on the same.
+// (32-bit divisions: two of 64 bits more had taken 0.3 us of every workgroup)
+__device__ __forceinline__ int64_t dense_share(int64_t total, uint32_t grid, uint32_t cus) {
+  if (total >= (int64_t)grid * 256) return (total + grid - 1) / grid;
+  const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);  // (uniform, below 2^20)
+  const uint32_t w = (t + 255) / 256, over = w % cus;
+  if (w > cus && over * 8 > cus * 3) return 256;
+  const uint32_t parts = max(w - over, cus);
+  return max((t + parts - 1) / parts, 192u);
 }
 __device__ __forceinline__ int64_t split_units(const AttnArgs& a, int bg) {
   const int64_t n = group_tokens(a, bg);
-  return n > 0 ? n + split_rule(a).segment_cost : 0;
+  return n > 0 ? n + kSegmentCost : 0;
 }
 
 __device__ __forceinline__ void load_words(const uint16_t* p, uint32_t* w) {
@@ -281,12 +293,12 @@ void attn_splitk_kernel(AttnArgs a) {
     if (tid == 255) s_prefix[BG] = run;
     __syncthreads();
   }
-  const Split split = split_rule(a);
   const int64_t total = s_prefix[BG];
   // a small selection is not spread thinner than the smallest share per
   // workgroup: below that the fixed work of a workgroup and the partials the
   // combine must merge cost more than the extra workgroups stream
-  const int64_t share = max((total + gridDim.x - 1) / gridDim.x, split.min_share);
+  const int64_t share = a.dense ? dense_share(total, gridDim.x, (uint32_t)a.cus)
+                                : max((total + gridDim.x - 1) / gridDim.x, kSparseShare);
   if (blockIdx.x == 0) {  // for the combine: the split and the group offsets
     if (tid == 0) a.ameta[0] = share;
     for (int bg = tid; bg <= BG; bg += 256) a.ameta[1 + bg] = s_prefix[bg];
@@ -302,7 +314,7 @@ void attn_splitk_kernel(AttnArgs a) {
 
   for (int bg = bg0; bg < BG && s_prefix[bg] < t1; ++bg) {
     // the group's tokens follow its segment cost of setup in the split
-    const int64_t first = s_prefix[bg] + split.segment_cost;
+    const int64_t first = s_prefix[bg] + kSegmentCost;
     const int64_t seg_lo = max(t0, first) - first;
     const int64_t seg_hi = min(t1, s_prefix[bg + 1]) - first;
     if (seg_lo >= seg_hi) continue;  // no token of this group in the range
@@ -696,7 +708,7 @@ __global__ __launch_bounds__(512) void combine_kernel(AttnArgs a) {
     if (slice == 0) out[d] = 0.f;
     return;
   }
-  const int64_t w0 = (P0 + split_rule(a).segment_cost) / share, w1 = (P1 - 1) / share;
+  const int64_t w0 = (P0 + kSegmentCost) / share, w1 = (P1 - 1) / share;
   const int np = (int)min(w1 - w0 + 1, (int64_t)kMaxAttnGrid);
   const float* pb = a.partials + (bg + w0) * kPart;
   const float* pd = pb + h * kHeadDim + d;  // this thread's output dimension of partial 0
@@ -785,7 +797,7 @@ static hipError_t resident_t(int G, size_t lds, int* per) {
   }
 }
 
-hipError_t attn_resident_grid(int G, int n_groups, bool paged, int* grid) {
+hipError_t attn_resident_grid(int G, int n_groups, bool paged, int* grid, int* compute_units) {
   int dev = 0, cus = 0, per = 0;
   const size_t lds = ((size_t)n_groups + 1) * sizeof(int64_t);
   hipError_t e = hipGetDevice(&dev);
@@ -793,6 +805,7 @@ hipError_t attn_resident_grid(int G, int n_groups, bool paged, int* grid) {
   if (e != hipSuccess) return e;
   e = paged ? resident_t<true>(G, lds, &per) : resident_t<false>(G, lds, &per);
   *grid = (per > 0 ? per : 1) * (cus > 0 ? cus : 1);
+  if (compute_units) *compute_units = cus > 0 ? cus : 1;
   return e;
 }
 

@@ -132,6 +132,7 @@ struct AttnArgs {
   const int64_t* kv_indptr;
   const int64_t* seq_len;     // [B] or null
   int B, Hq, Hkv, Cm, dense;
+  int cus;                    // dense: compute units of the device
   int NV, kv_div;             // selection groups per sequence and KV head divisor (as in FitArgs)
   int64_t total, chunk_tokens, max_chunks;
   const int32_t* gmeta;
@@ -151,7 +152,7 @@ hipError_t launch_sample(const FitArgs& a, int split, int n_heads, bool paged, h
 hipError_t launch_fit_union(const FitArgs& a, int G, int n_groups, hipStream_t st);
 hipError_t launch_attn(const AttnArgs& a, int G, int grid, bool paged, hipStream_t st);
 hipError_t launch_combine(const AttnArgs& a, int G, hipStream_t st);
-hipError_t attn_resident_grid(int G, int n_groups, bool paged, int* grid);
+hipError_t attn_resident_grid(int G, int n_groups, bool paged, int* grid, int* compute_units = nullptr);
 hipError_t launch_stream_read(const void* buf, int64_t n16, int workgroups, uint32_t* sink, hipStream_t st);
 
 }  // namespace tactic

@@ -317,6 +317,25 @@ def test_eight_head_attention_tile_remainders(n, paged):
         s += m
 
 
+@pytest.mark.parametrize("n", [5952, 5953, 8000, 8001, 11072, 11073, 16192, 16193])
+@pytest.mark.parametrize("hq", [8, 32])
+def test_dense_shares_at_whole_numbers_per_compute_unit(n, hq):
+    """Dense decode where the split's units (tokens and 192 for each of 8 KV heads) reach one share of 192, one of
+    256, 1.375 (the last to be rounded down to one) and two of 256 per compute unit, of which there are 256.  Bound as
+    above."""
+    T = _T()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    K = torch.randn(8, n, 128, generator=g, device="cuda").to(torch.bfloat16)
+    V = torch.randn(8, n, 128, generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn(1, hq, 128, generator=g, device="cuda").to(torch.bfloat16)
+    out = T.DenseDecoder(T.RaggedBatch([n], hq, 8))(q, K, V)
+    for h in range(hq):
+        k, v = K[h * 8 // hq].double(), V[h * 8 // hq].double()
+        ref = torch.softmax(k @ q[0, h].double() / 128 ** 0.5, 0) @ v
+        assert (out[0, h].double() - ref).abs().max() <= 1e-5 * float(v.abs().max())
+
+
 def test_eight_head_attention_infinite_values():
     """An infinite value reaches the heads that give its token any weight as that infinity, and a weight that is
     exactly zero times it is NaN: as with one multiplication per weight."""
