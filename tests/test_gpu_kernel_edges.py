@@ -134,8 +134,9 @@ def test_kmeans_equal_scores_of_zero():
     assert got.perm.tolist() == [[0, 2, 1]] and got.clusters.offsets.tolist() == [[0, 2, 3]]
 
 
-def _decode(lens, ncl, hq, hkv, seed, sizes=None, union=1, target=0.9):
-    """A sparse decode over random keys with the given cluster sizes (default: even, some empty)."""
+def _decode(lens, ncl, hq, hkv, seed, sizes=None, union=1, target=0.9, tail=None, change=None):
+    """A sparse decode over random keys with the given cluster sizes (default: random, some empty), `tail` recent
+    tokens per sequence behind the clusters; change(q, centroids) edits them in place."""
     T = _T()
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
@@ -145,17 +146,23 @@ def _decode(lens, ncl, hq, hkv, seed, sizes=None, union=1, target=0.9):
     V = torch.randn(hkv, total, 128, generator=g, device="cuda").to(torch.bfloat16)
     cen = torch.randn(hkv, sum(ncl), 128, generator=g, device="cuda").to(torch.bfloat16)
     off = []
-    for n, c in zip(lens, ncl):
+    tail = tail or [0] * len(lens)
+    for n, c in zip([n - t for n, t in zip(lens, tail)], ncl):
+        if c == 0:
+            off.append(np.zeros((hkv, 1), np.int64))
+            continue
         cuts = np.sort(rng.integers(0, n + 1, size=(hkv, c - 1)), axis=1) if sizes is None else \
             np.tile(np.cumsum(sizes)[:-1], (hkv, 1))
         off.append(np.concatenate([np.zeros((hkv, 1), np.int64), cuts, np.full((hkv, 1), n)], 1))
     offs = np.concatenate(off, 1).astype(np.int32)
     batch = T.RaggedBatch(lens, hq, hkv)
-    dec = T.SparseDecoder(batch, ncl, T.decode_params(target, use_union=union))
+    dec = T.SparseDecoder(batch, ncl, T.decode_params(target, use_union=union, max_tail=max(tail)))
     q = (0.3 * torch.randn(len(lens), hq, 128, generator=g, device="cuda")).to(torch.bfloat16)
+    if change:
+        change(q, cen)
     out, sq, skv = dec(q, K, V, T.ClusterSet(cen, torch.as_tensor(offs, device="cuda"), ncl))
     torch.cuda.synchronize()
-    return dict(q=q, K=K, V=V, off=off, out=out, sq=sq.cpu().numpy(), skv=skv.cpu().numpy(),
+    return dict(q=q, K=K, V=V, off=off, out=out, tail=tail, sq=sq.cpu().numpy(), skv=skv.cpu().numpy(),
                 view={k: v.cpu().numpy() for k, v in dec.view().items()}, batch=batch)
 
 
@@ -175,6 +182,9 @@ def _check_selection(r, lens, ncl, hq, hkv, union=1):
     G = hq // hkv
     v, c0 = r["view"], 0
     for b, (n, C) in enumerate(zip(lens, ncl)):
+        if C == 0:
+            assert not np.any(r["sq"][b]) and not torch.any(r["out"][b])
+            continue
         lengths = np.zeros((hq, C), np.int64)
         for h in range(hq):
             off = r["off"][b][h // G]
@@ -183,18 +193,20 @@ def _check_selection(r, lens, ncl, hq, hkv, union=1):
             assert np.array_equal(v["order"][b, h, :C], order), (b, h)
             pre = np.concatenate([[0], np.cumsum(size[order])])
             assert np.array_equal(v["rank_prefix"][b, h, :C + 1], pre), (b, h)
-            pos = _positions(n)
+            nc, tail = n - r["tail"][b], r["tail"][b]
+            pos = _positions(nc)
             rank = np.searchsorted(pre, pos, side="left") - 1  # the largest rank with fewer tokens ahead
             rows = off[order[rank]] + pos - 1 - pre[rank]
-            assert np.array_equal(v["sample_rows"][b, h, :len(pos)], rows), (b, h)
-            k = int(r["sq"][b, h])
+            rows = np.concatenate([rows, np.arange(nc, n)])  # then the recent tokens
+            assert np.array_equal(v["sample_rows"][b, h, :len(rows)], rows), (b, h)
+            k = int(r["sq"][b, h]) - tail
             lengths[h, order] = np.minimum(np.maximum(k - pre[:-1], 0), size[order])
         groups = [range(g * G, (g + 1) * G) for g in range(hkv)] if union else [[h] for h in range(hq)]
         for j, heads in enumerate(groups):
             want = lengths[list(heads)].max(0)
             assert np.array_equal(v["union_len"][j, c0:c0 + C], want), (b, j)
             if union:
-                assert r["skv"][b, j] == want.sum()
+                assert r["skv"][b, j] == want.sum() + r["tail"][b]
         c0 += C
 
 
@@ -210,6 +222,41 @@ def test_sort_two_heads_per_compute_unit():
     ncl = [4100, 8192, 1, 700, 1500, 3000, 4096, 5000, 1024]
     lens = [2 * c + 11 for c in ncl]
     _check_selection(_decode(lens, ncl, 32, 8, 5), lens, ncl, 32, 8)
+
+
+@pytest.mark.parametrize("lens,ncl,hq,hkv", [
+    ([70001], [32768], 64, 8),  # four workgroups per head, 8192 clusters each: two pieces
+    ([41000] * 4, [20000] * 4, 32, 8),  # two per head, 10000 clusters: two pieces
+    ([35003] * 8, [17000] * 8, 32, 8),  # one per head: three pieces
+    ([41000, 35000, 39999], [20000, 16500, 18001], 16, 4),  # five per head
+    ([50000, 6000], [20000, 3000], 8, 2),  # a short sequence among them
+    ([50000, 0, 40000], [20000, 0, 16500], 8, 2)])  # an empty one
+def test_sort_pieces(lens, ncl, hq, hkv):
+    """16385 to 32768 clusters: a head's buckets shared by several workgroups, each taking its share in pieces of
+    at most 6144 clusters."""
+    _check_selection(_decode(lens, ncl, hq, hkv, 3), lens, ncl, hq, hkv)
+
+
+@pytest.mark.parametrize("union", [1, 0])
+def test_sort_pieces_with_recent_tokens(union):
+    lens, ncl = [50000, 9000], [20000, 500]
+    _check_selection(_decode(lens, ncl, 8, 2, 4, tail=[300, 120], union=union), lens, ncl, 8, 2, union)
+
+
+@pytest.mark.parametrize("kind", ["equal", "bucket", "repeated"])
+@pytest.mark.parametrize("hq", [4, 96])
+def test_sort_pieces_fall_back(kind, hq):
+    """Heads of 20000 clusters that the pieces do not take (the head's first workgroup sorts them in the workspace):
+    all scores equal, or more than 6144 in a bucket; 96 heads: two workgroups each."""
+    def change(q, cen):
+        if kind == "equal":
+            q[0, ::2] = 0.0  # beside ordinary heads
+        elif kind == "bucket":
+            cen[:, 500:7500] = cen[:, 500:501]
+        else:
+            cen[:] = cen[:, torch.arange(cen.shape[1], device="cuda") % 3]
+    lens, ncl = [45000], [20000]
+    _check_selection(_decode(lens, ncl, hq, hq // 4, 5, change=change), lens, ncl, hq, hq // 4)
 
 
 @pytest.mark.parametrize("C,big", [(9, 1 << 19), (8193, 1 << 18), (20001, 70000)])
