@@ -303,7 +303,7 @@ def config_record(T, wl, Ps, dev, flush, reps: int, stage_ev, ceiling, host_grou
                     "attn_speedup_from_union": round(att_ph / ab_union[1], 3),
                     "kv_rows_per_head_over_union": round(int(skv_ph.sum()) / max(1, ab_union[2]), 3)}
         del dph
-    sort_path = "LDS" if max(ncl) <= 8192 else ("LDS pieces" if max(ncl) <= 32768 else "workspace")
+    sort_path = "LDS" if max(ncl) <= 16384 else ("LDS pieces" if max(ncl) <= 32768 else "workspace")
     out = {"batch": B, "seq_lens": (list(map(int, wl.seq_lens)) if B > 1 else int(wl.seq_lens[0])),
            "n_q_heads": Hq, "n_kv_heads": Hkv, "clusters_per_seq": (list(map(int, ncl)) if B > 1 else int(ncl[0])),
            "cluster_sort": sort_path, "kmeans_ms": round(km_ms, 2), "dense_us": round(us_dense, 2),

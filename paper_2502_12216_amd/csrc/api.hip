@@ -233,7 +233,6 @@ tactic_status tactic_sparse_decode_plan(const tactic_kv_shape* shape, const tact
   if (!p.sort_lds) {
     p.off_sort_keys = L.take(BH * p.nb_max * 8);
     p.off_sort_cnt = L.take(BH * (p.nb_max + 4) * 4);
-    p.off_sort_start = L.take(BH * (p.nb_max + 4) * 4);
   }
   p.ws_bytes = L.cur;
   // resident attention workgroups on the current device, so that decode calls
@@ -320,7 +319,6 @@ static tactic_status sparse_decode_impl(const uint16_t* q, const uint16_t* K_sor
   so.prm = sel_params(params);
   so.g_keys = p.sort_lds ? nullptr : reinterpret_cast<uint64_t*>(ws + p.off_sort_keys);
   so.g_cnt = p.sort_lds ? nullptr : reinterpret_cast<uint32_t*>(ws + p.off_sort_cnt);
-  so.g_start = p.sort_lds ? nullptr : reinterpret_cast<uint32_t*>(ws + p.off_sort_start);
   so.order = reinterpret_cast<int32_t*>(ws + p.off_order);
   so.rank_of = reinterpret_cast<int32_t*>(ws + p.off_rank);
   so.rprefix = reinterpret_cast<int32_t*>(ws + p.off_rprefix);

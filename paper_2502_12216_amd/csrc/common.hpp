@@ -23,8 +23,6 @@ struct Geometry {
   int exact;
 };
 
-__host__ __device__ inline int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
 // Tokens of sequence b: its span [indptr[b], indptr[b+1]) or, with a length
 // array, the first len[b] rows of that span.
 __device__ __forceinline__ int64_t seq_tokens(const int64_t* indptr, const int64_t* len, int b) {

@@ -196,9 +196,10 @@ __device__ __forceinline__ short4_t pair4(uint32_t lo, uint32_t hi) {
 
 // Four fp32 weights in [0, 1] as three bf16 operands whose sum is exact: the upper
 // 8 bits of the significand, the next 8 of the rest, the rest.  The second and
-// third of a weight that is not zero are at least 2^-126 (2^-126 of the
-// largest weight, below any rounding), so that its product with an infinite
-// value is that infinity, as in one multiplication, and not 0 x inf.
+// third of a weight that is not zero are at least 2^-126, so that its product
+// with an infinite value is that infinity, as in one multiplication, and not 0 x
+// inf; a row then adds at most 2^-125 of its value to a sum whose largest weight is
+// 1 (below the rounding of the output unless a value is 2^100 times the output).
 __device__ __forceinline__ void split_weights(const float (&p)[4], short4_t (&part)[3]) {
   uint32_t h[4], m[4], r[4];
 #pragma unroll

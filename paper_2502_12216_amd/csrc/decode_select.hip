@@ -20,43 +20,6 @@
 namespace tactic {
 
 // ============================================================================
-// Block-wide helpers (any blockDim that is a multiple of 64, at most 1024)
-// ============================================================================
-
-// Exclusive scan in place of a[0..count) (LDS or global); returns the total.
-// `s_wave` must hold 17 elements of T in LDS.  Ends with a barrier.
-template <typename T>
-__device__ T block_exclusive_scan(T* a, int count, T* s_wave) {
-  const int tid = threadIdx.x, nt = blockDim.x, nw = nt / kWave;
-  const int seg = (count + nt - 1) / nt;
-  const int beg = min(count, tid * seg), end = min(count, beg + seg);
-  T local = 0;
-  for (int i = beg; i < end; ++i) local += a[i];
-  T incl = wave_incl_scan(local);  // DPP, no LDS
-  if ((tid & (kWave - 1)) == kWave - 1) s_wave[tid / kWave] = incl;
-  __syncthreads();
-  if (tid == 0) {
-    T run = 0;
-    for (int w = 0; w < nw; ++w) {
-      const T t = s_wave[w];
-      s_wave[w] = run;
-      run += t;
-    }
-    s_wave[16] = run;
-  }
-  __syncthreads();
-  T run = s_wave[tid / kWave] + incl - local;
-  for (int i = beg; i < end; ++i) {
-    const T t = a[i];
-    a[i] = run;
-    run += t;
-  }
-  const T total = s_wave[16];
-  __syncthreads();
-  return total;
-}
-
-// ============================================================================
 // 1. Centroid scoring: s[b][h][j] = q_h . c_{b,g,j}, fp32 accumulation of
 //    bf16 products (v_dot2).  grid (ceil(Cm/kScoreRows), B*Hkv), 256 threads;
 //    16 lanes own one centroid row (16 B each), a wave scores 4 rows per step
@@ -852,7 +815,9 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
         c4[0] = make_uint4(0, 0, 0, 0);
         c4[1] = make_uint4(0, 0, 0, 0);
       }
-      // moments and range of the finite scores, as in the LDS path
+      // moments and range of the scores that are numbers, from the scores themselves
+      // (not from differences as in the other paths: a common offset large
+      // against the spread loses the variance, and the buckets crowd)
       float sm = 0.f, sq = 0.f, lo = INFINITY, hi = -INFINITY, nf = 0.f;
       for (int j0 = tid; j0 < C; j0 += kB * nt) {
         float v[kB];
@@ -1333,9 +1298,9 @@ __device__ bool positive_interval(double a, double b, int64_t lo, int64_t hi, in
 
 // 3a. Logits of the sampled rows: each lane sums its 8 bf16 products in fp32
 //     (v_dot2, error at most a few ulp of the lane's sum of |products|), the
-//     16 lane sums add in fp64.  grid (ceil(S_cap/128), B*Hq), 256 threads:
-//     workgroup c owns samples [128c, 128c + 128); 16 lanes per row, each wave
-//     gathers 32 rows with all loads in flight together.  The workgroup also
+//     16 lane sums add in fp64.  grid (ceil(S_cap/64), B*Hq), 256 threads:
+//     workgroup c owns samples [64c, 64c + 64); 16 lanes per row, each wave
+//     gathers 16 rows with all loads in flight together.  The workgroup also
 //     reduces its logits per region (exact head, window 1, window 2, recent
 //     tokens) to (max, sum of exp(l - max)), so the fit needs one exponential
 //     per chunk instead of one per sample.

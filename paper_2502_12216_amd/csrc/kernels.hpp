@@ -83,7 +83,6 @@ struct SortArgs {
   SelParams prm;
   uint64_t* g_keys;           // sort scratch when the sort does not fit LDS
   uint32_t* g_cnt;
-  uint32_t* g_start;
   int32_t* order;             // [B*Hq][Cm]
   int32_t* rank_of;           // [B*Hq][Cm]
   int32_t* rprefix;           // [B*Hq][Cm+1]

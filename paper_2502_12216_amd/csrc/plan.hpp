@@ -38,7 +38,8 @@ struct DecodePlan {
   // workspace byte offsets
   int64_t off_scores, off_order, off_rank, off_rprefix, off_headmeta, off_rows, off_logit;
   int64_t off_fit, off_cut, off_union_len, off_gmeta, off_rstart, off_rupos, off_cfr, off_lse;
-  int64_t off_partials, off_sort_keys, off_sort_cnt, off_sort_start, off_ameta, off_slice_tot;
+  // (unused0 keeps the places of the fields behind it)
+  int64_t off_partials, off_sort_keys, off_sort_cnt, unused0, off_ameta, off_slice_tot;
   int64_t ws_bytes;
   int64_t exact_bp, win_bp, win_min, p1_bp, p2_bp;
   int64_t events[kStageEvents];  // optional hipEvent_t recorded between the kernels

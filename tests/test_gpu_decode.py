@@ -200,18 +200,20 @@ def test_sparse_single_cluster_and_target_one_is_dense():
     check_layer(inp1, lay1, 0.9, res1, label="one cluster")
 
 
-@pytest.mark.parametrize("case", ["lds", "shared"])
+@pytest.mark.parametrize("case", ["lds", "sliced", "shared"])
 def test_sparse_is_deterministic(case):
-    """Two calls give bit-identical outputs and counts: the in-LDS sort, and
-    12000 clusters per sequence, where workgroups share each head's sort (a
-    cluster's place inside its bucket follows the order of atomic arrivals,
-    which may differ between calls) and each group's union runs in slices."""
+    """Two calls give bit-identical outputs and counts: the in-LDS sort,
+    12000 clusters per sequence, where each group's union runs in slices, and
+    20000, where workgroups share each head's sort (a cluster's place inside
+    its bucket follows the order of atomic arrivals, which may differ between
+    calls)."""
     import dataclasses
     if case == "lds":
         wl = _small("ctx32k_llama8b", [5000, 2500])
     else:
-        base = _small("ctx32k_llama8b", [30000, 12000])
-        wl = dataclasses.replace(base, fixed_clusters=12000, name=f"{base.name}_c12000_det")
+        C, lens = {"sliced": (12000, [30000, 12000]), "shared": (20000, [50000, 20000])}[case]
+        base = _small("ctx32k_llama8b", lens)
+        wl = dataclasses.replace(base, fixed_clusters=C, name=f"{base.name}_c{C}_det")
     inp = synth.make_layer(wl, 0)
     lay = synth.label_layout(inp)
     a = run_sparse(inp, lay, 0.9)
@@ -492,14 +494,13 @@ def test_sparse_target_one_at_128k_matches_dense_and_paged():
 
 @pytest.mark.parametrize("case", ["c34000", "big_bucket", "big_cluster", "empty_seq"])
 def test_sparse_sort_general_workspace_path(case):
-    """Heads that the LDS-piece sort of 8192 < C <= 32768 clusters hands to
-    the general workspace path: more than 32768 clusters (34000 clusters of
-    about two tokens), a bucket larger than a piece (7000 of 9000 clusters of
-    sequence 0 share one centroid, so 7000 equal scores), and a cluster of
-    more than 65535 tokens (cluster 0 of every KV head holds 70000 of 90000
-    tokens); and an empty sequence with no clusters between two of 9000
-    clusters (its heads take no piece and must return zeros).  Staged parity
-    on every group at P = 0.9."""
+    """The general workspace path of the sort (34000 clusters of about two
+    tokens: more than 32768), and on the sort in LDS of 8193 to 16384
+    clusters a crowded bucket (7000 of 9000 clusters of sequence 0 share one
+    centroid, so 7000 equal scores), a cluster of more than 65535 tokens
+    (cluster 0 of every KV head holds 70000 of 90000 tokens), and an empty
+    sequence with no clusters between two of 9000 (its heads must return
+    zeros).  Staged parity on every group at P = 0.9."""
     import dataclasses
     P = 0.9
     lens, C = {"c34000": ([70000], 34000), "big_bucket": ([20000, 12000], 9000),
@@ -528,13 +529,11 @@ def test_sparse_sort_general_workspace_path(case):
 
 @pytest.mark.parametrize("Hq,Hkv", [(32, 8), (16, 2)])
 def test_sparse_union_range_writers(Hq, Hkv):
-    """Unions of more than 8192 clusters. With 8 heads per group (16 / 2) the
-    group's one workgroup writes the ranges one of two ways: from each
-    thread's 32-cluster segment when at most an eighth of the clusters are
-    non-empty, else in a coalesced pass over the clusters; with 4 heads (32 /
-    8) and in per-head mode the union runs in slices with a second kernel for
-    the ranges. 9000 clusters of about two tokens at a low and a high target
-    give both densities (asserted from the union lengths), in union and
+    """Unions of more than 8192 clusters: with 8 heads per group (16 / 2),
+    with 4 (32 / 8) and in per-head mode the union runs in slices with a
+    second kernel for the ranges. 9000 clusters of about two tokens at a low
+    and a high target give few non-empty clusters (at most an eighth) and
+    many (asserted from the union lengths), in union and
     per-head modes and with 300 recent tokens after the clusters of sequence
     0 (their range follows the clusters' ranges), with staged parity on
     every group."""
@@ -562,14 +561,13 @@ def test_sparse_union_range_writers(Hq, Hkv):
 @pytest.mark.parametrize("case", ["pieces", "workspace", "mixed", "odd_split"])
 def test_sparse_large_sort_paths_with_recent_tail(case):
     """Recent tokens after the clusters on the sorts of more than 8192
-    clusters: 12000 clusters (LDS pieces) and 34000 clusters (workspace
+    clusters: 12000 clusters (all in LDS) and 34000 clusters (workspace
     path), with a tail of 200 and 150 tokens on the first sequence (its
     sampled rows follow the windows', its range follows the union's), and a
     batch that mixes 12000 clusters with 3000 (the smaller sequence's heads
-    then take the pieces, shared by the same number of workgroups, with a
-    tail of 100), and three sequences of 16 / 4 heads at 9000 clusters (48
-    heads: five workgroups share each head's sort, five slices of 1800
-    clusters each per-head union), in union and per-head modes, staged parity
+    then run with the larger one's slots, with a tail of 100), and three
+    sequences of 16 / 4 heads at 9000 clusters (48 per-head unions of five
+    slices of 1800 clusters each), in union and per-head modes, staged parity
     on every group at P = 0.9."""
     import dataclasses
     T = _tactic()
@@ -590,8 +588,8 @@ def test_sparse_large_sort_paths_with_recent_tail(case):
 
 @pytest.mark.parametrize("P", [0.5, 0.9])
 def test_sparse_degenerate_scores_out_of_lds_sort(P):
-    """The sort of more than 8192 clusters per head runs out of the
-    workspace: a zero query (all scores equal: identity order), centroids
+    """The sort of 8193 to 16384 clusters per head, in LDS with 16-bit ids
+    and bucket ends: a zero query (all scores equal: identity order), centroids
     repeated every 8 clusters (eight scores shared by an eighth of the
     clusters each: crowded buckets, ties by cluster id) and ordinary heads,
     with 9000 clusters of about two tokens each (many empty)."""

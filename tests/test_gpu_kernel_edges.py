@@ -340,6 +340,14 @@ def test_union_of_eight_heads(C, target):
     _check_selection(_decode(lens, ncl, 8, 1, C, target=target), lens, ncl, 8, 1)
 
 
+@pytest.mark.parametrize("C,hq,union", [(49152, 8, 1), (49153, 8, 1), (65536, 4, 1), (65537, 4, 1), (65537, 2, 0)])
+def test_union_beyond_the_slices(C, hq, union):
+    """Eight slices hold 49152 clusters of 8 heads, 65536 of fewer; beyond, one workgroup per group takes passes
+    over memory."""
+    lens, ncl = [2 * C, 700], [C, 40]
+    _check_selection(_decode(lens, ncl, hq, 1, 6, union=union), lens, ncl, hq, 1, union)
+
+
 @pytest.mark.parametrize("n", [1, 3, 4, 63, 64, 65, 127, 255, 513, 4099])
 @pytest.mark.parametrize("paged", [False, True])
 def test_eight_head_attention_tile_remainders(n, paged):
