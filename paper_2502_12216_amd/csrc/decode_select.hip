@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void score_clusters_kernel(ScoreArgs a) {
 //    bucket start plus the number of smaller keys in its bucket.  The map
 //    takes the standardised score z = (s - mean) / sd to log2(1 + |z|) on each
 //    side of the mean, which spreads a bell-shaped score distribution with far
-//    outliers over the buckets (at most about 1.5 times the mean load), where a
+//    outliers over the buckets (at most about three times the mean load), where a
 //    linear map over [min, max] would crowd the bulk into a few buckets.  Then
 //    the tokens ahead of every rank (exclusive prefix of cluster sizes in rank
 //    order) and the rows of the sampled positions: exact head 1..N and the
@@ -121,6 +121,21 @@ __device__ __forceinline__ int score_bucket(float s, float mu, float inv_sd, int
   const uint32_t x = min(__float_as_uint(1.0f + fabsf(z)) - 0x3f800000u, 3u * (1u << 23) - 1u);
   const int i = (int)__umulhi(x << 7, half * 4u / 3u);
   return z >= 0.f ? (int)half - 1 - i : (int)half + i;
+}
+
+// The map of the workspace sort: (nb / 2) r for z >= 0 and nb - (nb / 2) r for z < 0
+// with r = 1 / (1 + |z|), every step monotone as above.  The division costs
+// little there, where every other key of a bucket is a read from memory, and a
+// normal distribution fills a bucket to at most 1.9 times the mean (2.9 above):
+// 66000 clusters x 32 heads, whole decode, 1.43 ms with score_bucket, 1.26 so (scores
+// with far outliers 1.73, 1.29).
+__device__ __forceinline__ int squash_bucket(float s, float mu, float inv_sd, int nb) {
+  if (!(s == s)) return nb - 1;
+  const float z = (s - mu) * inv_sd;
+  const float half = 0.5f * (float)nb;
+  const float x = half * (1.0f / (1.0f + fabsf(z)));  // (0, nb / 2], non-increasing in |z|
+  const int bk = (int)(z >= 0.f ? x : (float)nb - x);
+  return min(max(bk, 0), nb - 1);
 }
 
 // Sum of a wave total per wave of 1024 threads, in every lane (a scalar).
@@ -266,6 +281,7 @@ constexpr int kPieceBuckets = 4096;
 constexpr int kPiecePer = 6;                    // entries per thread in the piece scan
 constexpr int kPieceCap = kPiecePer * 1024;     // clusters per piece
 constexpr int kPieceMaxC = 32 * 1024;           // 32 clusters per thread
+constexpr uint32_t kCrowd = 64;                 // clusters of a bucket from which on the compact sort reads four at a time
 constexpr size_t kPieceLdsBytes = (size_t)kPieceBuckets * 8 + (size_t)kPieceCap * 20;
 constexpr int kPieceOrdAt = kPieceBuckets * 8 + kPieceCap * 12;  // LDS offsets: ids by rank in the piece,
 constexpr int kPieceSizeAt = kPieceOrdAt + kPieceCap * 4;        // sizes, then prefix, by rank
@@ -283,7 +299,7 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
   __shared__ uint32_t s_wave_u[17];
   __shared__ float s_wave_f[17];
   __shared__ __align__(16) float s_red[16][4];
-  __shared__ int s_any_n;  // workspace sort: clusters of the piece collected so far
+  __shared__ int s_any_n;  // workspace sort: clusters of the piece collected so far; compact sort: a crowded bucket
   const int tid = threadIdx.x, nt = blockDim.x;
   const int bh = blockIdx.x;
   const int b = bh / a.Hq, h = bh % a.Hq, g = h / a.G;
@@ -378,6 +394,7 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
       far = fmaxf(far, fabsf(d));
       nf += (int)__popcll(__ballot(v[e] == v[e]));
     }
+    if (kCompact && tid == 0) s_any_n = 0;
     score_moments(pivot, sm, sq, nf, far, C, s_red, &mu, &inv_sd, &all_equal);
     if (all_equal) {
       // all scores equal: the order is the cluster id
@@ -399,9 +416,13 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
           const uint4 x = reinterpret_cast<const uint4*>(ends)[(tid * kE / 2 + e) / 4];
           w[e] = x.x, w[e + 1] = x.y, w[e + 2] = x.z, w[e + 3] = x.w;
         }
-        uint32_t local = 0, all;
+        uint32_t local = 0, all, bits = 0;
 #pragma unroll
-        for (int e = 0; e < kE / 2; ++e) local += (w[e] & 0xffffu) + (w[e] >> 16);
+        for (int e = 0; e < kE / 2; ++e) {
+          local += (w[e] & 0xffffu) + (w[e] >> 16);
+          bits |= w[e];
+        }
+        if (bits & (0x10001u * (0x10000u - kCrowd))) s_any_n = 1;  // a count with a bit at or above kCrowd's
         uint32_t run = block_base(local, s_wave_u, &all);
 #pragma unroll
         for (int e = 0; e < kE / 2; ++e) {
@@ -424,27 +445,52 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
         }
       }
       __syncthreads();
+      if (s_any_n) {
+        // some bucket holds kCrowd clusters or more: keys and ids together, four per
+        // step in 16- and 8-byte reads (97 distinct scores among 16384 clusters x 32
+        // heads, whole decode: key by key 912 us, 364 so)
 #pragma unroll
-      for (int e = 0; e < kE; ++e) {
-        const int j = tid + e * 1024;
-        pos[e] = 0;
-        if (j < C) {
-          const uint32_t key = desc_key_bits(v[e]);
-          const uint32_t end = end16[bk[e]], beg = bk[e] > 0 ? end16[bk[e] - 1] : 0u;
-          uint32_t r = 0, eq = 0, t = beg;
-          for (; t + 1 < end; t += 2) {  // two LDS reads in flight per step
-            const uint32_t k0 = keys32[t], k1 = keys32[t + 1];
-            r += (k0 < key ? 1u : 0u) + (k1 < key ? 1u : 0u);
-            eq += (k0 == key ? 1u : 0u) + (k1 == key ? 1u : 0u);
+        for (int e = 0; e < kE; ++e) {
+          const int j = tid + e * 1024;
+          pos[e] = 0;
+          if (j < C) {
+            const uint32_t key = desc_key_bits(v[e]);
+            const uint32_t end = end16[bk[e]], beg = bk[e] > 0 ? end16[bk[e] - 1] : 0u;
+            auto less = [&](uint32_t k, uint32_t id) { return k < key || (k == key && id < (uint32_t)j) ? 1u : 0u; };
+            uint32_t r = 0, t = beg;
+            for (; t < end && (t & 3); ++t) r += less(keys32[t], ids[t]);
+            for (; t + 4 <= end; t += 4) {
+              const uint4 k = *reinterpret_cast<const uint4*>(keys32 + t);
+              const uint2 i = *reinterpret_cast<const uint2*>(ids + t);
+              r += less(k.x, i.x & 0xffffu) + less(k.y, i.x >> 16) + less(k.z, i.y & 0xffffu) + less(k.w, i.y >> 16);
+            }
+            for (; t < end; ++t) r += less(keys32[t], ids[t]);
+            pos[e] = (int)(beg + r);
           }
-          if (t < end) {
-            const uint32_t k0 = keys32[t];
-            r += k0 < key ? 1u : 0u;
-            eq += k0 == key ? 1u : 0u;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < kE; ++e) {
+          const int j = tid + e * 1024;
+          pos[e] = 0;
+          if (j < C) {
+            const uint32_t key = desc_key_bits(v[e]);
+            const uint32_t end = end16[bk[e]], beg = bk[e] > 0 ? end16[bk[e] - 1] : 0u;
+            uint32_t r = 0, eq = 0, t = beg;
+            for (; t + 1 < end; t += 2) {  // two LDS reads in flight per step
+              const uint32_t k0 = keys32[t], k1 = keys32[t + 1];
+              r += (k0 < key ? 1u : 0u) + (k1 < key ? 1u : 0u);
+              eq += (k0 == key ? 1u : 0u) + (k1 == key ? 1u : 0u);
+            }
+            if (t < end) {
+              const uint32_t k0 = keys32[t];
+              r += k0 < key ? 1u : 0u;
+              eq += k0 == key ? 1u : 0u;
+            }
+            if (eq > 1)  // equal scores besides its own: by id
+              for (t = beg; t < end; ++t) r += keys32[t] == key && ids[t] < j ? 1u : 0u;
+            pos[e] = (int)(beg + r);
           }
-          if (eq > 1)  // equal scores besides its own: by id
-            for (t = beg; t < end; ++t) r += keys32[t] == key && ids[t] < j ? 1u : 0u;
-          pos[e] = (int)(beg + r);
         }
       }
       __syncthreads();
@@ -867,7 +913,7 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
           for (int e = 0; e < kB; ++e) v[e] = sc[min(j0 + e * nt, C - 1)];
 #pragma unroll
           for (int e = 0; e < kB; ++e)
-            if (j0 + e * nt < C) atomicAdd(&cnt_l[score_bucket(v[e], mu, inv_sd, nb)], 1u);
+            if (j0 + e * nt < C) atomicAdd(&cnt_l[squash_bucket(v[e], mu, inv_sd, nb)], 1u);
         }
         __syncthreads();
         {
@@ -885,7 +931,7 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
           for (int e = 0; e < kB; ++e) {
             const int j = j0 + e * nt;
             if (j < C)
-              keys[atomicAdd(&start_l[score_bucket(v[e], mu, inv_sd, nb)], 1u)] =
+              keys[atomicAdd(&start_l[squash_bucket(v[e], mu, inv_sd, nb)], 1u)] =
                   ((uint64_t)desc_key_bits(v[e]) << 32) | (uint32_t)j;
           }
         }
@@ -908,7 +954,7 @@ __device__ __forceinline__ void sort_head(const SortArgs a) {
             key[e] = ((uint64_t)desc_key_bits(sv) << 32) | (uint32_t)jc;
             o_lo[e] = off[jc];
             o_hi[e] = off[jc + 1];
-            const int bk = all_equal ? 0 : score_bucket(sv, mu, inv_sd, nb);
+            const int bk = all_equal ? 0 : squash_bucket(sv, mu, inv_sd, nb);
             end[e] = all_equal ? 1u : start_l[bk];
             beg[e] = all_equal ? 0u : end[e] - cnt_l[bk];
             r[e] = 0;

@@ -224,6 +224,18 @@ def test_sort_two_heads_per_compute_unit():
     _check_selection(_decode(lens, ncl, 32, 8, 5), lens, ncl, 32, 8)
 
 
+@pytest.mark.parametrize("ncl,hq,hkv", [([9001], 4, 1), ([16384], 4, 1), ([4100, 8192, 1, 700, 1500, 3000, 4096, 5000, 1024], 32, 8),
+                                        ([33000], 4, 1)])
+@pytest.mark.parametrize("distinct", [1, 3, 97, 400])
+def test_sort_of_repeated_scores(ncl, hq, hkv, distinct):
+    """Few distinct scores: buckets of tens to thousands of clusters, equal ones by id, on the sorts with 16-bit ids
+    (8193 to 16384 clusters; more than 256 heads) and in the workspace."""
+    def change(q, cen):
+        cen[:] = cen[:, torch.arange(cen.shape[1], device="cuda") % distinct]
+    lens = [2 * c + 11 for c in ncl]
+    _check_selection(_decode(lens, ncl, hq, hkv, 8, change=change), lens, ncl, hq, hkv)
+
+
 @pytest.mark.parametrize("lens,ncl,hq,hkv", [
     ([70001], [32768], 64, 8),  # four workgroups per head, 8192 clusters each: two pieces
     ([41000] * 4, [20000] * 4, 32, 8),  # two per head, 10000 clusters: two pieces
