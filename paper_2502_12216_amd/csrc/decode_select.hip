@@ -166,12 +166,13 @@ __device__ __forceinline__ void score_moments(float pivot, float sm, float sq, i
   sq = sum16(r.y);
   const float n = sum16(r.z);
   *all_equal = sum16(r.w) == 0.f && n == (float)C;
+  *inv_sd = 1.f;
   const float inv_n = 1.f / fmaxf(n, 1.f), m = sm * inv_n;
   const float var = fmaxf(sq * inv_n - m * m, 0.f);
   *mu = pivot + m;
   if (var > 0.f && var < INFINITY) {  // (the same in all threads)
     *inv_sd = 1.f / sqrtf(var);
-  } else {
+  } else if (!*all_equal) {
     far = wave_allmax_f(far);
     __syncthreads();  // the sums are read
     if ((threadIdx.x & (kWave - 1)) == 0) s_red[wave][0] = far;
