@@ -672,8 +672,8 @@ __device__ __forceinline__ void sort_members(const int32_t* list, int m, uint32_
 
 // The workgroup (1024 threads) sorts a cluster's m members (tokens below n) by a
 // bitmap of the tokens in s_bits (kBitTokens / 32 words), window by window: into
-// `out`, with their ranks.  A list of 32768 of 65536 tokens: about 12 us (one wave
-// with windows of 16384 tokens 1.2 ms).  Begins and ends with a barrier.
+// `out`, with their ranks.  Bound by the passes over the list and the words, a few
+// memory round trips each.  Begins and ends with a barrier.
 __device__ __forceinline__ void sort_by_bitmap(const int32_t* list, int m, int n, uint32_t* s_bits, int32_t* out, int32_t* rank,
                                                int* s_w) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -735,8 +735,8 @@ __device__ __forceinline__ void sort_by_bitmap(const int32_t* list, int m, int n
 // clusters of up to kRankMax members, the workgroup sorts each larger one by a
 // bitmap, and the four chains' waves sum it.  A wave for each of them (windows of
 // 16384 tokens, 16 rows in flight) had made one iteration slower than counting
-// tiles and a wave per mean: 65536 x 8 keys of which half are zero, ten iterations
-// 37.1 ms, now 12.5 (25.3 by tiles); 131072 x 8 keys, one iteration, 1 / 16 / 256 clusters
+// tiles and a wave per mean: 65536 x 8 keys of which half are zero, first update 4.54
+// ms, now 1.20, ten iterations 37.1 ms, now 12.3 (25.3 by tiles); 131072 x 8 keys, one iteration, 1 / 16 / 256 clusters
 // 12.5 / 4.7 / 1.14 ms, now 3.0 / 1.1 / 0.73 (7.6 / 2.7 / 0.73); 81 distinct keys among 65536, two
 // iterations 1.20 ms, now 0.66 (1.04).
 // grid (slices, BG), 1024 threads; per: clusters per slice

@@ -327,7 +327,7 @@ def test_sort_of_extreme_scores(C, kind):
 
 def test_sort_time_of_tiny_or_equal_infinite_scores():
     """8192 clusters whose scores' squares underflow, or which are all infinite: the buckets of the sort must not
-    crowd (quadratic work: 40 times an ordinary call).  A bound of three ordinary calls."""
+    crowd (quadratic work: 18 to 35 times an ordinary call).  A bound of three ordinary calls."""
     def us(kind):
         dec, q, K, cl = _scored(_kinds(kind, 8192))
         best = float("inf")
